@@ -96,14 +96,8 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = {"rk4_resident": ("evolve_resident.hip", "device_common.h", "ftwa_internal.h"),
+KERNEL_SOURCES = {"rk4_resident": ("rk4_resident.h", "device_common.h", "ftwa_internal.h"),
                   "rk4_stage_stream": ("evolve_stream.hip", "device_common.h", "ftwa_internal.h")}
-
-
-# Sections of a kernel's source files that define other kernels only (their
-# own templates, not instantiated by this kernel): left out of its hash.
-KERNEL_SOURCE_SKIP = {"rk4_resident": (b"// " + b"-" * 64 + b" split kernel",
-                                       b"// " + b"-" * 64 + b" configurations")}
 
 
 def kernel_source_hash(kernel: str) -> str:
@@ -111,14 +105,9 @@ def kernel_source_hash(kernel: str) -> str:
     layouts): counters taken on other sources are not reported."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2212_04352_amd", "csrc")
-    skip = KERNEL_SOURCE_SKIP.get(kernel)
     for f in KERNEL_SOURCES[kernel]:
         with open(os.path.join(csrc, f), "rb") as fh:
-            text = fh.read()
-        if skip and skip[0] in text:
-            i = text.index(skip[0])
-            text = text[:i] + text[text.index(skip[1], i):]
-        h.update(f.encode() + text)
+            h.update(f.encode() + fh.read())
     return h.hexdigest()[:16]
 
 

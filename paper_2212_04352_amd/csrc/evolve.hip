@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cstring>
 #include <map>
+#include <set>
 #include <mutex>
 #include <string>
 #include <tuple>
@@ -101,6 +102,7 @@ struct LaunchDesc {                // one resident launch: a group in a pass
 
 struct GroupPlan {
     int config = -1;
+    int threads = 0, units = 1, workers = 0;
     size_t lds = 0;
     int Nmax = 0;
     std::vector<int> members;
@@ -164,19 +166,24 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
     p.drop_partners = tune && tune->drop_partners;
 
     // ---- path and configuration of every instance
-    // 8 config + 4 (general interaction) + 2 (complex hopping) + (external potential)
-    std::map<int, int> group_of_config;
+    // (8 config + 4 (general interaction) + 2 (complex hopping) + (external
+    // potential), threads, units, workers)
+    std::map<std::tuple<int, int, int, int>, int> group_of_config;
     for (int k = 0; k < n_inst; ++k) {
         InstPlan ip;
         const DeviceTables& tab = host_tables(inst[k].lat);
         const int N = inst[k].lat->N;
         int cfg = force;
+        int shared_cfg = -1;      // a tuned shared-pack configuration
+        bool tuned_tile = false;  // another resident configuration was tuned
         bool tuned_stream = false;
         if (cfg < 0 && want == FTWA_PATH_AUTO) {
             int c = -1;
             if (tuned_config(N, class_shape(tab), dtype, &c)) {
                 if (c < 0) tuned_stream = true;
-                cfg = c;
+                if (resident_is_shared(c)) shared_cfg = c;
+                else cfg = c;
+                tuned_tile = c >= 0 && !resident_is_shared(c);
             }
         }
         // an external potential: the stream kernels, or a resident configuration
@@ -215,6 +222,14 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             can_res = resident_has_potential(c0) &&
                       resident_plan(N, dtype, tab, &ip.res, c0, inst[k].inv == nullptr, true);
         }
+        // Small lattices whose shared-pack form fits (with the instance's
+        // variant) run there; whether the resident path takes the instance at
+        // all was decided above.
+        if (can_res && force < 0 && !tuned_tile && inst[k].inv == nullptr) {
+            ResidentPlan sp;
+            if (shared_plan(N, dtype, tab, inst[k].n_traj, &sp, shared_cfg, pot, hop, gint))
+                ip.res = sp;
+        }
         if (force >= 0 && !can_res)
             return fail(FTWA_ENOTSUP, hop    ? "the forced resident configuration has no "
                                                "complex-hopping variant or does not fit"
@@ -228,12 +243,17 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             // instances with a potential form groups of their own: their
             // launches run the potential variant, whose LDS layout holds the
             // profile and is sized for it
-            const int key = 8 * ip.res.config + (gint ? 4 : 0) + (hop ? 2 : 0) + (pot ? 1 : 0);
+            const auto key = std::make_tuple(
+                8 * ip.res.config + (gint ? 4 : 0) + (hop ? 2 : 0) + (pot ? 1 : 0),
+                ip.res.threads, ip.res.units, ip.res.workers);
             auto it = group_of_config.find(key);
             if (it == group_of_config.end()) {
                 it = group_of_config.emplace(key, (int)p.groups.size()).first;
                 GroupPlan g;
                 g.config = ip.res.config;
+                g.threads = ip.res.threads;
+                g.units = ip.res.units;
+                g.workers = ip.res.workers;
                 p.groups.push_back(g);
             }
             ip.group = it->second;
@@ -295,7 +315,8 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         } else {
             // whole rounds of the trajectories the group runs at once
             const int64_t align = std::max<int64_t>(
-                1, resident_concurrency(ip.res.config, p.groups[ip.group].lds));
+                1, resident_concurrency(ip.res.config, p.groups[ip.group].lds, ip.res.threads,
+                                        ip.res.units));
             c = (M + n_pass_goal - 1) / n_pass_goal;
             c = (c + align - 1) / align * align;
         }
@@ -342,7 +363,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
                 int64_t m0, Mc;
                 window(p, inst[k], k, j, &m0, &Mc);
                 if (Mc <= 0) continue;
-                const int64_t per = resident_item_traj(g.config);
+                const int64_t per = g.units;
                 L.n_items += (Mc + per - 1) / per;
                 L.work += (double)Mc * n_steps;
                 if (inst[k].lat->t != 1.0) L.unit_hop = false;
@@ -353,7 +374,8 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             }
             entry += L.n_entries;
             g.max_items = std::max(g.max_items, L.n_items);
-            L.grid = resident_grid(g.config, g.lds, std::max<int64_t>(L.n_items, 1));
+            L.grid = resident_grid(g.config, g.lds, std::max<int64_t>(L.n_items, 1), g.threads,
+                                   g.units);
             p.launches.push_back(L);
         }
     p.n_table = entry;
@@ -378,13 +400,13 @@ ftwa_status build_table(Plan& p, const ftwa_instance* inst, char* ws) {
     for (int j = 0; j < p.n_pass; ++j)
         for (const GroupPlan& g : p.groups) {
             int64_t item0 = 0;
-            const int64_t per = resident_item_traj(g.config);
+            const int64_t per = g.units;
             for (int k : g.members) {
                 int64_t m0, Mc;
                 window(p, inst[k], k, j, &m0, &Mc);
                 if (Mc <= 0) continue;
                 const InstPlan& ip = p.inst[k];
-                ResidentInst e;
+                ResidentInst e = {};
                 e.N = inst[k].lat->N;
                 e.P = (int)packed_count(e.N);
                 e.Mc = Mc;
@@ -398,6 +420,10 @@ ftwa_status build_table(Plan& p, const ftwa_instance* inst, char* ws) {
                                            (int)cplx_bytes(p.dtype), &e.desc, &e.part_words,
                                            &e.hmax)) != FTWA_OK)
                         return st;
+                } else if (resident_is_shared(g.config)) {
+                    if ((st = shared_lists(inst[k].lat, ip.res.lanes, ip.res.workers / ip.res.lanes,
+                                           (int)ip.res.even_slots, &e.stab)) != FTWA_OK)
+                        return st;
                 } else if ((st = padded_descriptors(inst[k].lat, ip.res.even_slots,
                                                     ip.res.odd_slots, (int)cplx_bytes(p.dtype),
                                                     resident_spins(g.config) == 1, &e.desc)) !=
@@ -409,6 +435,7 @@ ftwa_status build_table(Plan& p, const ftwa_instance* inst, char* ws) {
                 e.ord = tab.ord;
                 e.nb = tab.nb;
                 e.dpos = tab.dpos;
+                e.n_a = tab.n_a;
                 e.t = inst[k].lat->t;
                 e.U = inst[k].U;
                 e.X = reinterpret_cast<double*>(ws + ip.off_x);
@@ -553,6 +580,9 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
             L.n_entries = Ld.n_entries;
             L.n_items = Ld.n_items;
             L.grid = Ld.grid;
+            L.threads = g.threads;
+            L.units = g.units;
+            L.workers = g.workers;
             L.Nmax = g.Nmax;
             L.dt = p.dt;
             L.n_steps = p.n_steps;
@@ -747,6 +777,7 @@ ftwa_status ftwa_lattice_upload(ftwa_lattice lat) {
             for (bool pot : {false, true}) {
                 ResidentPlan rp;
                 if (!resident_plan(N, dtype, tab, &rp, c, true, pot)) continue;
+                if (resident_is_shared(c)) continue;
                 const int eb = (int)cplx_bytes(dtype);
                 const void* d = nullptr;
                 std::string key;
@@ -770,6 +801,14 @@ ftwa_status ftwa_lattice_upload(ftwa_lattice lat) {
                 }
                 if ((st = resident_prepare(c, rp.lds)) != FTWA_OK) return st;
             }
+    std::vector<std::array<int, 3>> shapes;
+    std::set<int> ready;
+    for (const ResidentPlan& rp : shared_plans(N, tab)) {
+        shapes.push_back({rp.lanes, rp.workers / rp.lanes, (int)rp.even_slots});
+        if (!ready.insert(rp.config).second) continue;
+        if ((st = resident_prepare(rp.config, rp.lds)) != FTWA_OK) return st;
+    }
+    if ((st = upload_shared(lat, shapes)) != FTWA_OK) return st;
     return FTWA_OK;
 }
 
@@ -960,7 +999,7 @@ ftwa_status plan_probe(const ftwa_instance& in, ftwa_dtype dtype, int probe_step
         ResidentPlan rp;
         if (!resident_plan(N, dtype, tab, &rp, c)) continue;
         pr.cands.push_back(c);
-        want = std::max(want, 2 * resident_concurrency(c, rp.lds));
+        want = std::max(want, 2 * resident_concurrency(c, rp.lds, rp.threads, rp.units));
     }
     pr.cands.push_back(-1);
     if (want == 0) want = kStreamChunk;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdint>
 #include <map>
 #include <tuple>
@@ -47,6 +48,7 @@ struct DeviceTables {
     int32_t* dpos = nullptr;   // [N]: site -> its position in the sublattice-major
                                // diagonal (the sites of one sublattice, ascending,
                                // then the other's)
+    int n_a = 0;               // sites of the first sublattice
     SplitShape split[kMaxParts + 1];  // by part count G = 2..kMaxParts (bipartite only)
     uint4* rdesc = nullptr;    // [2P][2]: descriptors of the on-chip reverse sweep with a
                                // packed X (N <= kReverseMaxSites; see reverse_descriptors)
@@ -92,6 +94,10 @@ struct ftwa_lattice_s {
     // resident-path descriptors padded per class to whole slots, by
     // (device, even slots, odd slots, element bytes and diagonal layout)
     std::map<std::tuple<int, int64_t, int64_t, int>, void*> padded;
+    // shared-pack lists by (device, lanes per element, entries per pass, entries)
+    // in one allocation per device
+    std::map<std::tuple<int, int, int, int>, const uint32_t*> shared;
+    std::map<int, void*> shared_dev;
     std::vector<uint32_t> class_order;      // a | b << 16 of the stored elements in LDS-slot order
     std::vector<int32_t> diag_pos;          // site -> sublattice-major diagonal position
     std::vector<int32_t> rank;              // site -> bandwidth-reducing rank
@@ -162,6 +168,23 @@ std::string padded_key(int dev, int64_t even_slots, int64_t odd_slots, int elem_
 ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd_slots,
                                int elem_bytes, bool compact, const void** out,
                                bool create = false);
+
+// Row stride (in elements) of the shared-pack kernel's blocks where I lanes
+// share an element: at least the larger sublattice and odd (its own inverse
+// modulo 16 / I); I = 1: 7 or 9 modulo 16 (their own inverses, as are 1 and
+// 15, which do not spread the triangle a < b evenly over the residues of
+// a S + b).
+__host__ __device__ inline int shared_stride(int N, int n_a, int I) {
+    const int n_b = N - n_a;
+    int s = n_a > n_b ? n_a : n_b;
+    while (I == 1 ? s % 16 != 7 && s % 16 != 9 : s % 2 == 0) ++s;
+    return s;
+}
+// Lists of the shared-pack kernel where I lanes share an element: n_list
+// entries per class, the diagonal among the first n_pass (evolve_shared.h).
+ftwa_status shared_lists(ftwa_lattice lat, int I, int n_pass, int n_list, const uint32_t** out);
+// Uploads them for every {I, n_pass, n_list} of shapes (ftwa_lattice_upload).
+ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>>& shapes);
 
 // Tables of the split resident kernel for G parts (uploaded once per shape by
 // ftwa_lattice_upload).
@@ -285,9 +308,11 @@ struct ResidentPlan {
     int config = -1;
     int spins_per_unit = 2;  // 1: one spin block per workgroup, pairs exchange diagonals
     int threads = 0;
-    int units = 1;
+    int units = 1;           // trajectories per item of the schedule (spin split: 1)
     int64_t even_slots = 0;  // descriptor padding of the even / odd class
     int64_t odd_slots = 0;
+    int workers = 0;         // shared-pack configurations: threads that own elements
+    int lanes = 1;           // shared-pack configurations: lanes that share an element
     int64_t bnd_entry = 0;   // split configurations: first boundary entry of the even class
     size_t lds = 0;
     bool u_lds = false;      // shared blocks with a general interaction: lds includes a copy
@@ -320,6 +345,8 @@ struct ResidentInst {
     const void* hop;       // NULL or the complex-hopping ratio table (hop_table)
     const void* umat;      // NULL or the general interaction in the working precision (umat_table)
     int u_lds;             // nonzero: the shared-block kernel copies umat into LDS per item
+    int n_a;               // shared-pack kernel: sites of the first sublattice
+    const uint32_t* stab;  // shared-pack kernel: the dealt lists (shared_lists)
 };
 struct ResidentLaunch {
     int config;
@@ -327,7 +354,8 @@ struct ResidentLaunch {
     const ResidentInst* table;  // device
     int n_entries;
     int64_t n_items;
-    int64_t grid;               // resident_grid(config, lds, n_items), fixed at plan time
+    int threads, units, workers;  // ResidentPlan's
+    int64_t grid;               // resident_grid(...), fixed at plan time
     int Nmax;
     double dt;
     int64_t n_steps;
@@ -344,8 +372,8 @@ struct ResidentLaunch {
     bool interaction;           // every entry carries a general interaction (the GINT variant)
 };
 // Picks the first kernel configuration that fits (or only `force_config` if >= 0).
-// allow_split: the split configurations may be chosen (they keep no
-// invariant sums); need_potential, need_hop, need_interaction: only
+// allow_split: configurations that keep no invariant sums may be chosen (the
+// split and the shared-pack ones); need_potential, need_hop, need_interaction: only
 // configurations with an external-potential, complex-hopping or
 // general-interaction variant (the FP32 spin split and the FP64 split kernel).
 bool resident_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, ResidentPlan* plan,
@@ -370,10 +398,19 @@ ftwa_status umat_table(const double* u_mat, int N, ftwa_dtype dtype, void* out,
 // zero (queued on stream).
 ftwa_status hop_table(const double* hop_w, const int32_t* nb, const int32_t* dpos, int N,
                       int64_t n_steps, ftwa_dtype dtype, void* out, hipStream_t stream);
-int64_t resident_item_traj(int config);      // trajectories per item of the schedule
 int64_t resident_max_pairs();
-int64_t resident_concurrency(int config, size_t lds);  // trajectories in flight at once
-int64_t resident_grid(int config, size_t lds, int64_t n_items);
+// trajectories in flight at once; threads, units: ResidentPlan's
+int64_t resident_concurrency(int config, size_t lds, int threads, int units);
+int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int units);
+// The shared-pack kernel's configuration (evolve_shared.h) for a lattice and
+// Hamiltonian variant and an ensemble of n_traj trajectories, or only
+// force_config's; false if none fits.
+bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_traj,
+                 ResidentPlan* plan, int force_config, bool need_potential, bool need_hop,
+                 bool need_interaction);
+// Every plan that shared_plan may return for a lattice (repetitions included).
+std::vector<ResidentPlan> shared_plans(int N, const DeviceTables& tab);
+bool resident_is_shared(int config);
 size_t resident_mailbox_bytes(int config, int Nmax, int64_t n_items);
 ftwa_status resident_prepare(int config, size_t lds);  // host only, not under graph capture
 ftwa_status resident_launch(const ResidentLaunch& L, hipStream_t stream);

@@ -6,6 +6,7 @@
 #include <deque>
 #include <map>
 #include <set>
+#include <unordered_map>
 #include <utility>
 
 #include "ftwa_internal.h"
@@ -235,7 +236,7 @@ ftwa_status ftwa_lattice_info(ftwa_lattice lat, int* n_sites, int* n_bonds, cons
 
 void ftwa_free_lattice(ftwa_lattice lat) {
     if (!lat) return;
-    if (lat->dev.empty() && lat->padded.empty() && lat->split.empty()) {
+    if (lat->dev.empty() && lat->padded.empty() && lat->split.empty() && lat->shared_dev.empty()) {
         delete lat;  // never uploaded: no HIP call
         return;
     }
@@ -258,6 +259,10 @@ void ftwa_free_lattice(ftwa_lattice lat) {
     for (auto& [key, val] : lat->split) {
         if (hipSetDevice(std::get<0>(key)) != hipSuccess) continue;
         (void)hipFree(std::get<0>(val));
+    }
+    for (auto& [dev, ptr] : lat->shared_dev) {
+        if (hipSetDevice(dev) != hipSuccess) continue;
+        (void)hipFree(ptr);
     }
     if (cur >= 0) (void)hipSetDevice(cur);
     delete lat;
@@ -317,7 +322,7 @@ namespace ftwa {
 // non-bipartite graph.
 bool build_class_order(ftwa_lattice lat, std::vector<uint32_t>* order, int64_t* n_even,
                        std::vector<int32_t>* diag_pos, int64_t* n_gen_even,
-                       int64_t* n_gen_odd, std::vector<int32_t>* rank_out) {
+                       int64_t* n_gen_odd, std::vector<int32_t>* rank_out, int* n_a) {
     const int N = lat->N;
     std::vector<int> colour(N, -1);
     for (int root = 0; root < N; ++root) {
@@ -336,9 +341,11 @@ bool build_class_order(ftwa_lattice lat, std::vector<uint32_t>* order, int64_t* 
     }
     diag_pos->assign(N, 0);
     int next = 0;
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < 2; ++c) {
         for (int i = 0; i < N; ++i)
             if (colour[i] == c) (*diag_pos)[i] = next++;
+        if (c == 0) *n_a = next;
+    }
 
     // Cuthill-McKee rank of every site (each connected component in turn)
     std::vector<int> rank(N, -1);
@@ -891,7 +898,7 @@ void compute_host_tables(ftwa_lattice lat) {
     std::vector<int32_t> dpos;
     std::vector<int32_t> rank;
     tab.bipartite = build_class_order(lat, &order, &tab.n_even, &dpos, &tab.n_gen_even,
-                                      &tab.n_gen_odd, &rank);
+                                      &tab.n_gen_odd, &rank, &tab.n_a);
     if (tab.bipartite) {
         lat->class_order = order;
         lat->diag_pos = dpos;
@@ -951,6 +958,249 @@ std::vector<uint4> reverse_descriptors(const ftwa_lattice_s& lat, bool full) {
                 q1.w = (uint32_t)e;
             }
     return out;
+}
+
+namespace {
+
+// One entry of a shared-pack list and the LDS elements it touches: itself,
+// its six neighbours and, for an even one, its transpose.
+struct SharedEntry {
+    uint32_t code;      // a | b << 8
+    uint32_t unit[8];
+    uint8_t shape[7];   // elements 1..7 against element 0, modulo 16 (see shared_deal)
+};
+
+std::vector<SharedEntry> shared_entries(const ftwa_lattice_s& L, bool odd, int I) {
+    const int N = L.N, n_a = L.host.n_a, S = shared_stride(N, n_a, I);
+    std::vector<int> site(N);
+    for (int i = 0; i < N; ++i) site[L.diag_pos[i]] = i;
+    auto nb = [&](int pos, int n) -> int {
+        const int i = site[pos];
+        return n < L.deg[i] ? L.diag_pos[L.nbr[(size_t)i * kMaxDeg + n]] : -1;
+    };
+    const int bb = n_a * S, ab = N * S;
+    const uint32_t zero = (uint32_t)(((N + n_a) * S + 15) / 16 * 16);
+    std::vector<SharedEntry> out;
+    auto add = [&](int a, int b) {
+        SharedEntry e;
+        e.code = (uint32_t)a | (uint32_t)b << 8;
+        const bool b_cls = !odd && a >= n_a;
+        const int pc = b_cls ? a : b, pr = b_cls ? b : a;  // whose neighbours c and r run over
+        e.unit[0] = (uint32_t)(odd ? ab + a * S + b - n_a
+                                   : b_cls ? bb + (a - n_a) * S + b - n_a : a * S + b);
+        e.unit[7] = odd ? e.unit[0]
+                        : (uint32_t)(b_cls ? bb + (b - n_a) * S + a - n_a : b * S + a);
+        for (int n = 0; n < 3; ++n) {
+            const int kc = nb(pc, n), kr = nb(pr, n);
+            int c, r;
+            if (odd) {
+                c = a * S + kc;
+                r = bb + (kr - n_a) * S + b - n_a;
+            } else if (!b_cls) {
+                c = ab + a * S + kc - n_a;
+                r = ab + b * S + kr - n_a;
+            } else {
+                c = ab + kc * S + b - n_a;
+                r = ab + kr * S + a - n_a;
+            }
+            e.unit[1 + n] = kc < 0 ? zero + (e.unit[0] & 15u) : (uint32_t)c;
+            e.unit[4 + n] = kr < 0 ? zero + (e.unit[0] & 15u) : (uint32_t)r;
+        }
+        for (int k = 1; k < 8; ++k) {
+            const bool missing = e.unit[k] >= zero;
+            // an even element's r and transpose follow S times its own address
+            const uint32_t of = !odd && k >= 4 && !missing ? (uint32_t)S * e.unit[0] : e.unit[0];
+            e.shape[k - 1] = (uint8_t)(missing ? 16 : ((e.unit[k] - of) & 15u));
+        }
+        out.push_back(e);
+    };
+    if (odd) {
+        for (int a = 0; a < n_a; ++a)
+            for (int b = n_a; b < N; ++b) add(a, b);
+        return out;
+    }
+    for (int a = 0; a < N; ++a) add(a, a);  // the diagonal first
+    for (int c = 0; c < 2; ++c)
+        for (int a = c ? n_a : 0; a < (c ? N : n_a); ++a)
+            for (int b = a + 1; b < (c ? N : n_a); ++b) add(a, b);
+    return out;
+}
+
+// Deals entries to list positions so that the 16-lane groups in which LDS
+// serves 16-byte accesses -- lanes 0-3, 12-15, 20-27 and 4-11, 16-19, 28-31 of
+// either half of a wave, I lanes per entry -- touch different elements modulo
+// M = 16 / I in every access.  The element of every access is own or S own
+// plus the entry's shape (modulo M), so M entries of one shape with different
+// own elements modulo M are free of conflicts; the others go into groups
+// picked one by one.  The first n_diag entries (the diagonal) lead the list,
+// `per` to a group (half of any diagonal's own elements meet modulo M).  With
+// I >= 16 no order has conflicts.
+std::vector<uint32_t> shared_deal(const std::vector<SharedEntry>& all, size_t n_diag, int I,
+                                  size_t per) {
+    std::vector<uint32_t> out;
+    if (I >= 16) {
+        for (const SharedEntry& e : all) out.push_back(e.code);
+        return out;
+    }
+    const size_t M = (size_t)(16 / I);
+    const uint32_t mask = (uint32_t)M - 1;
+    // positions (of the 2 M of a half wave) of either group's entries; I = 8:
+    // entries 0, 3 and 1, 2 meet in both groups
+    std::vector<size_t> places[2];
+    static const bool kSide[8] = {false, true, true, false, true, false, false, true};
+    for (size_t k = 0; k < 2 * M; ++k)
+        places[I == 8 ? k == 1 || k == 2 : kSide[k * (size_t)I / 4]].push_back(k);
+    std::vector<std::vector<size_t>> groups;
+    std::vector<size_t> g;
+    uint32_t used[8][16];
+    auto open_group = [&]() {
+        g.clear();
+        std::memset(used, 0xff, sizeof(used));
+    };
+    auto fits = [&](size_t k, int limit) {
+        int c = 0;
+        for (int x = 0; x < 8 && c <= limit; ++x) {
+            const uint32_t u = all[k].unit[x], was = used[x][u & mask];
+            c += was != 0xffffffffu && was != u;
+        }
+        return c <= limit;
+    };
+    // up to `most` entries of `from` into the open group, those with at most
+    // `limit` clashing accesses, looking at the first `window`
+    auto pick = [&](std::vector<size_t>& from, size_t most, int limit, size_t window) {
+        size_t kept = 0, p = 0;
+        for (; p < from.size() && p < window && g.size() < most; ++p) {
+            const size_t k = from[p];
+            if (fits(k, limit)) {
+                for (int x = 0; x < 8; ++x) used[x][all[k].unit[x] & mask] = all[k].unit[x];
+                g.push_back(k);
+            } else {
+                from[kept++] = k;
+            }
+        }
+        if (kept < p) from.erase(from.begin() + (std::ptrdiff_t)kept, from.begin() + (std::ptrdiff_t)p);
+    };
+    constexpr size_t kWindow = 512;
+    std::vector<size_t> diag(n_diag), rest;
+    for (size_t k = 0; k < n_diag; ++k) diag[k] = k;
+    for (size_t k = n_diag; k < all.size(); ++k) rest.push_back(k);
+    while (!diag.empty()) {
+        open_group();
+        pick(diag, M, 0, diag.size());
+        for (int limit = 1; limit <= 8; ++limit) pick(diag, per, limit, diag.size());
+        for (int limit = 0; limit <= 8; ++limit) pick(rest, M, limit, limit ? kWindow / 4 : kWindow);
+        groups.push_back(g);
+    }
+    // the rest by shape (5 bits a neighbour) and own element, in the order in
+    // which the shapes appear
+    std::vector<std::vector<size_t>> by;  // M lists per shape
+    std::unordered_map<uint64_t, size_t> index;
+    for (size_t k : rest) {
+        uint64_t sh = 0;
+        for (uint8_t x : all[k].shape) sh = sh << 5 | (x == 16 ? 16u : x & mask);
+        const size_t n = index.try_emplace(sh, index.size()).first->second;
+        if (by.size() < (n + 1) * M) by.resize((n + 1) * M);
+        by[n * M + (all[k].unit[0] & mask)].push_back(k);
+    }
+    rest.clear();
+    for (size_t n = 0; n < by.size(); n += M) {
+        size_t full = by[n].size();
+        for (size_t r = 1; r < M; ++r) full = std::min(full, by[n + r].size());
+        for (size_t x = 0; x < full; ++x) {
+            g.clear();
+            for (size_t r = 0; r < M; ++r) g.push_back(by[n + r][x]);
+            groups.push_back(g);
+        }
+        for (size_t r = 0; r < M; ++r)
+            rest.insert(rest.end(), by[n + r].begin() + (std::ptrdiff_t)full, by[n + r].end());
+    }
+    std::sort(rest.begin(), rest.end());
+    while (!rest.empty()) {
+        open_group();
+        for (int limit = 0; limit <= 8; ++limit) pick(rest, M, limit, limit ? kWindow / 4 : kWindow);
+        groups.push_back(g);
+    }
+    // within a group by own element, the two groups of 32 lanes a quarter
+    // turn apart: 16-byte writes go eight lanes at a time over 128 bytes
+    out.assign((groups.size() + 1) / 2 * 2 * M, 0xffffffffu);
+    for (size_t n = 0; n < groups.size(); ++n) {
+        const uint32_t turn = n % 2 ? (uint32_t)M / 4 : 0u;
+        std::sort(groups[n].begin(), groups[n].end(), [&](size_t a, size_t b) {
+            const uint32_t ra = (all[a].unit[0] - turn) & mask, rb = (all[b].unit[0] - turn) & mask;
+            return ra != rb ? ra < rb : a < b;
+        });
+        for (size_t k = 0; k < groups[n].size(); ++k)
+            out[n / 2 * 2 * M + places[n % 2][k]] = all[groups[n][k]].code;
+    }
+    return out;
+}
+
+}  // namespace
+
+ftwa_status shared_lists(ftwa_lattice lat, int I, int n_pass, int n_list, const uint32_t** out) {
+    int dev = 0;
+    FTWA_HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lock(lat->mu);
+    auto it = lat->shared.find(std::make_tuple(dev, I, n_pass, n_list));
+    if (it == lat->shared.end())
+        return fail(FTWA_EINVAL,
+                    "the lattice's tables are not on this device: call ftwa_lattice_upload first");
+    *out = it->second;
+    return FTWA_OK;
+}
+
+ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>>& shapes) {
+    int dev = 0;
+    FTWA_HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lock(lat->mu);
+    if (shapes.empty() || lat->shared_dev.count(dev)) return FTWA_OK;
+    const int N = lat->N;
+    std::vector<uint32_t> head((size_t)2 * N);  // sites, neighbours' positions
+    for (int i = 0; i < N; ++i) {
+        uint32_t w = 0xffffffu;
+        for (int k = 0; k < lat->deg[i]; ++k) {
+            w &= ~(0xffu << (8 * k));
+            w |= (uint32_t)lat->diag_pos[lat->nbr[(size_t)i * kMaxDeg + k]] << (8 * k);
+        }
+        head[lat->diag_pos[i]] = (uint32_t)i;
+        head[N + lat->diag_pos[i]] = w;
+    }
+    std::map<std::array<int, 3>, size_t> at;
+    std::map<std::pair<int, size_t>, std::vector<uint32_t>> dealt[2];  // (I, per)
+    std::vector<uint32_t> t;
+    for (const auto& shape : shapes) {
+        if (at.count(shape)) continue;
+        const int I = shape[0];
+        const size_t n_pass = (size_t)shape[1], n_list = (size_t)shape[2];
+        at[shape] = t.size();
+        t.insert(t.end(), head.begin(), head.end());
+        // the diagonal within the first pass
+        const size_t M = I >= 16 ? 1 : (size_t)(16 / I);
+        const size_t per = ((size_t)N + n_pass / M - 1) / (n_pass / M);
+        for (int odd = 0; odd < 2; ++odd) {
+            auto [d, fresh] = dealt[odd].try_emplace({I, odd ? 0 : per});
+            if (fresh)
+                d->second = shared_deal(shared_entries(*lat, odd != 0, I),
+                                        odd ? 0 : (size_t)N, I, per);
+            const size_t end = t.size() + n_list;
+            if (d->second.size() > n_list)
+                return fail(FTWA_EINVAL, "shared-pack lists exceed their shape");
+            t.insert(t.end(), d->second.begin(), d->second.end());
+            t.resize(end, 0xffffffffu);
+        }
+    }
+    void* mem = nullptr;
+    FTWA_HIP_TRY(hipMalloc(&mem, t.size() * sizeof(uint32_t)));
+    if (hipMemcpy(mem, t.data(), t.size() * sizeof(uint32_t), hipMemcpyHostToDevice) !=
+        hipSuccess) {
+        (void)hipFree(mem);
+        return fail(FTWA_EHIP, "copying the shared-pack lists");
+    }
+    lat->shared_dev[dev] = mem;
+    for (const auto& [shape, off] : at)
+        lat->shared[std::make_tuple(dev, shape[0], shape[1], shape[2])] =
+            static_cast<const uint32_t*>(mem) + off;
+    return FTWA_OK;
 }
 
 ftwa_status upload_tables(ftwa_lattice lat) {
