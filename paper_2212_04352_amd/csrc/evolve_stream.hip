@@ -319,38 +319,57 @@ ftwa_status stream_step(const StreamChunk& c, const DeviceTables& tab, ftwa_dtyp
 
 namespace {
 
-// One thread per trajectory walks every packed element of both spins (the
-// element index is uniform, so loads are coalesced over trajectories) and
-// accumulates in FP64: hop_s = sum_i sum_{k in nb(i)} Re rho_ik (each bond
-// twice) and frob_s = sum_ij |rho_ij|^2.
+// hop_s = sum_i sum_{k in nb(i)} Re rho_ik (each bond twice) and
+// frob_s = sum_ij |rho_ij|^2, accumulated in FP64.
+//
+// Bound by reading the state once.  A workgroup takes 8 trajectories of one
+// spin (64 or 128 contiguous bytes per element) and deals the elements to 128
+// lanes each, so that a few hundred trajectories fill the chip and a lane has
+// several loads in flight; the bonds, a few hundred elements, are read again
+// from the cache.  The partial sums of a trajectory meet in a fixed order.
+// 150 sites FP64, 500 trajectories (181 MB): 72 us, 2.5 TB/s (one thread per
+// trajectory, elements one after another: 10.9 ms).
+constexpr int kInvTraj = 8, kInvLanes = 128;
+
 template <typename T>
-__global__ __launch_bounds__(256) void record_inv_kernel(int N, int64_t P, int64_t Mc,
-                                                         const cplx_t<T>* __restrict__ y,
-                                                         int64_t ldy,
-                                                         const uint32_t* __restrict__ elem,
-                                                         const int32_t* __restrict__ nb,
-                                                         double* __restrict__ parts) {
-    const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= Mc) return;
-    for (int s = 0; s < 2; ++s) {
-        double hop = 0.0, frob = 0.0;
-        for (int64_t p = 0; p < P; ++p) {
+__global__ __launch_bounds__(kInvTraj * kInvLanes) void record_inv_kernel(
+    int N, int64_t P, int64_t Mc, const cplx_t<T>* __restrict__ y, int64_t ldy,
+    const uint32_t* __restrict__ elem, const int32_t* __restrict__ nb,
+    double* __restrict__ parts) {
+    const int x = (int)threadIdx.x % kInvTraj, lane = (int)threadIdx.x / kInvTraj;
+    const int s = (int)blockIdx.y;
+    const int64_t m = (int64_t)blockIdx.x * kInvTraj + x;
+    double hop = 0.0, frob = 0.0;
+    if (m < Mc) {
+        const cplx_t<T>* const ys = y + (int64_t)s * P * ldy + m;
+#pragma unroll 4
+        for (int p = lane; p < (int)P; p += kInvLanes) {
             const uint32_t ij = elem[p];
-            const int i = (int)(ij & 0xffffu), j = (int)(ij >> 16);
-            const cplx_t<T> v = y[((int64_t)s * P + p) * ldy + m];
+            const cplx_t<T> v = ys[(int64_t)p * ldy];
             const double re = (double)v.x, im = (double)v.y;
-            if (i == j) {
-                frob += re * re;
-            } else {
-                frob += 2.0 * (re * re + im * im);
-                const int d = nb[i * 4 + 3];
-                bool bond = false;
-                for (int n = 0; n < d; ++n) bond = bond || nb[i * 4 + n] == j;
-                if (bond) hop += 2.0 * re;
-            }
+            frob += (ij & 0xffffu) == ij >> 16 ? re * re : 2.0 * (re * re + im * im);
         }
-        parts[(s * 2) * Mc + m] = hop;
-        parts[(s * 2 + 1) * Mc + m] = frob;
+        for (int e = lane; e < 4 * N; e += kInvLanes) {
+            const int i = e / 4, n = e % 4, j = n < nb[i * 4 + 3] ? nb[e] : -1;
+            if (n == 3 || j <= i) continue;
+            hop += 2.0 * (double)ys[((int64_t)i * N - (int64_t)i * (i - 1) / 2 + j - i) * ldy].x;
+        }
+    }
+    for (int d = kInvTraj; d < 64; d *= 2) {
+        hop += __shfl_xor(hop, d);
+        frob += __shfl_xor(frob, d);
+    }
+    constexpr int kWaves = kInvTraj * kInvLanes / 64;
+    __shared__ double part[2][kWaves][kInvTraj];
+    if (threadIdx.x % 64 < kInvTraj) {
+        part[0][threadIdx.x / 64][x] = hop;
+        part[1][threadIdx.x / 64][x] = frob;
+    }
+    __syncthreads();
+    if (lane < 2 && m < Mc) {
+        double sum = 0.0;
+        for (int w = 0; w < kWaves; ++w) sum += part[lane][w][x];
+        parts[(s * 2 + lane) * Mc + m] = sum;
     }
 }
 
@@ -358,7 +377,7 @@ __global__ __launch_bounds__(256) void record_inv_kernel(int N, int64_t P, int64
 
 ftwa_status record_inv(const StreamChunk& c, const DeviceTables& tab, ftwa_dtype dtype,
                        double* parts, hipStream_t stream) {
-    const dim3 grid((unsigned)((c.Mc + 255) / 256)), block(256);
+    const dim3 grid((unsigned)((c.Mc + kInvTraj - 1) / kInvTraj), 2), block(kInvTraj * kInvLanes);
     if (dtype == FTWA_F64)
         hipLaunchKernelGGL(record_inv_kernel<double>, grid, block, 0, stream, c.N, c.P, c.Mc,
                            static_cast<const double2*>(c.y), c.ldy, tab.elem, tab.nb, parts);
