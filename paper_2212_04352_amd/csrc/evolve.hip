@@ -85,6 +85,7 @@ struct InstPlan {
     size_t off_x = 0, off_inv = 0; // resident: this instance's record regions
     size_t off_hop = 0;            // resident with complex hopping: its ratio table
     size_t off_umat = 0;           // resident with a general interaction: u in dtype
+    bool by_record = false;        // resident: a launch per record interval (see plan_evolve)
 };
 
 struct LaunchDesc {                // one resident launch: a group in a pass
@@ -105,6 +106,7 @@ struct GroupPlan {
     int threads = 0, units = 1, workers = 0;
     size_t lds = 0;
     int Nmax = 0;
+    bool by_record = false;        // one member, a launch per record interval
     std::vector<int> members;
     int64_t max_items = 0;
     size_t off_mb = 0;
@@ -144,7 +146,8 @@ void window(const Plan& p, const ftwa_instance& in, int k, int j, int64_t* m0, i
 }
 
 ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_t n_steps,
-                        int record_every, ftwa_dtype dtype, const ftwa_tuning* tune, Plan* out) {
+                        int record_every, ftwa_dtype dtype, const ftwa_tuning* tune, Plan* out,
+                        bool allow_by_record = true) {
     if (dtype != FTWA_F64 && dtype != FTWA_F32) return fail(FTWA_EINVAL, "unknown dtype");
     if (n_steps < 0) return fail(FTWA_EINVAL, "n_steps < 0");
     if (record_every < 1) return fail(FTWA_EINVAL, "record_every < 1");
@@ -167,8 +170,9 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
 
     // ---- path and configuration of every instance
     // (8 config + 4 (general interaction) + 2 (complex hopping) + (external
-    // potential), threads, units, workers)
-    std::map<std::tuple<int, int, int, int>, int> group_of_config;
+    // potential), threads, units, workers, 1 + the instance if it is launched
+    // per record interval)
+    std::map<std::tuple<int, int, int, int, int>, int> group_of_config;
     for (int k = 0; k < n_inst; ++k) {
         InstPlan ip;
         const DeviceTables& tab = host_tables(inst[k].lat);
@@ -199,29 +203,29 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         if (n_var > 1 && (want == FTWA_PATH_RESIDENT || force >= 0))
             return fail(FTWA_ENOTSUP, "a potential, complex hopping and a general interaction "
                                       "together run on the stream path only");
-        bool can_res = !tuned_stream && n_var <= 1 &&
-                       resident_plan(N, dtype, tab, &ip.res, cfg, inst[k].inv == nullptr);
-        if (gint && can_res) {
-            // the configuration chosen for the on-site U, if it has the variant
+        auto fits = [&](bool allow_split) {
+            if (tuned_stream || n_var > 1 ||
+                !resident_plan(N, dtype, tab, &ip.res, cfg, allow_split))
+                return false;
+            // the configuration chosen for the on-site U, real hopping and no
+            // potential, if it has the instance's variant (else the stream path)
             const int c0 = ip.res.config;
-            can_res = resident_has_interaction(c0) &&
-                      resident_plan(N, dtype, tab, &ip.res, c0, inst[k].inv == nullptr, false,
-                                    false, true);
-        }
-        if (hop && can_res) {
-            // the configuration chosen for real hopping, if it has the variant
-            const int c0 = ip.res.config;
-            can_res = resident_has_hop(c0) &&
-                      resident_plan(N, dtype, tab, &ip.res, c0, inst[k].inv == nullptr, false,
-                                    true);
-        }
-        if (pot && can_res) {
-            // the configuration chosen without the potential, if it has the
-            // potential variant (else the stream path)
-            const int c0 = ip.res.config;
-            can_res = resident_has_potential(c0) &&
-                      resident_plan(N, dtype, tab, &ip.res, c0, inst[k].inv == nullptr, true);
-        }
+            if ((gint && !resident_has_interaction(c0)) || (hop && !resident_has_hop(c0)) ||
+                (pot && !resident_has_potential(c0)))
+                return false;
+            return n_var == 0 ||
+                   resident_plan(N, dtype, tab, &ip.res, c0, allow_split, pot, hop, gint);
+        };
+        bool can_res = fits(inst[k].inv == nullptr);
+        // The split configurations keep no invariant sums.  With monitors the
+        // automatic path launches them once per record interval and sums the
+        // stored state in between: a launch reads and writes the state once,
+        // where the stream kernels do so several times a stage (150 sites
+        // FP64, 500 trajectories, 50 steps, 6 records: 48.0 ms there, 11.3 ms
+        // so; 20 steps with a record after each 21.1 and 13.8 ms, with 64
+        // trajectories 3.9 and 3.9 ms).
+        if (!can_res && inst[k].inv && allow_by_record && force < 0 && want == FTWA_PATH_AUTO)
+            can_res = ip.by_record = fits(true);
         // Small lattices whose shared-pack form fits (with the instance's
         // variant) run there; whether the resident path takes the instance at
         // all was decided above.
@@ -245,7 +249,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             // profile and is sized for it
             const auto key = std::make_tuple(
                 8 * ip.res.config + (gint ? 4 : 0) + (hop ? 2 : 0) + (pot ? 1 : 0),
-                ip.res.threads, ip.res.units, ip.res.workers);
+                ip.res.threads, ip.res.units, ip.res.workers, ip.by_record ? 1 + k : 0);
             auto it = group_of_config.find(key);
             if (it == group_of_config.end()) {
                 it = group_of_config.emplace(key, (int)p.groups.size()).first;
@@ -254,6 +258,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
                 g.threads = ip.res.threads;
                 g.units = ip.res.units;
                 g.workers = ip.res.workers;
+                g.by_record = ip.by_record;
                 p.groups.push_back(g);
             }
             ip.group = it->second;
@@ -439,7 +444,9 @@ ftwa_status build_table(Plan& p, const ftwa_instance* inst, char* ws) {
                 e.t = inst[k].lat->t;
                 e.U = inst[k].U;
                 e.X = reinterpret_cast<double*>(ws + ip.off_x);
-                e.inv_parts = inst[k].inv ? reinterpret_cast<double*>(ws + ip.off_inv) : nullptr;
+                e.inv_parts = inst[k].inv && !ip.by_record
+                                  ? reinterpret_cast<double*>(ws + ip.off_inv)
+                                  : nullptr;
                 e.item0 = item0;
                 item0 += (Mc + per - 1) / per;
                 e.dump = p.dump ? static_cast<char*>(p.dump) + (size_t)m0 * cplx_bytes(p.dtype)
@@ -460,6 +467,49 @@ ftwa_status build_table(Plan& p, const ftwa_instance* inst, char* ws) {
     }
     for (const GroupPlan& g : p.groups)
         if ((st = resident_prepare(g.config, g.lds)) != FTWA_OK) return st;
+    return FTWA_OK;
+}
+
+// A resident launch per record interval, the invariant sums of the state
+// before the first and after each full one.  L: the launch of the whole run,
+// whose only table entry is rewritten for every interval (its records and its
+// potential's envelope start where the interval does; monitors exclude complex
+// hopping and a general interaction).
+ftwa_status launch_by_record(const Plan& p, const ftwa_instance& in, int k, const LaunchDesc& Ld,
+                             ResidentLaunch L, char* ws, hipStream_t stream, KernelTimer& timer) {
+    ftwa_status st;
+    const InstPlan& ip = p.inst[k];
+    const ResidentInst& e = p.table[(size_t)Ld.first_entry];
+    DeviceTables tab;
+    if ((st = device_tables(in.lat, &tab)) != FTWA_OK) return st;
+    StreamChunk c;
+    c.N = e.N;
+    c.P = e.P;
+    c.Mc = e.Mc;
+    c.y = e.rho;
+    c.ldy = e.ldr;
+    double* const parts = reinterpret_cast<double*>(ws + ip.off_inv);
+    if ((st = record_inv(c, tab, p.dtype, parts, stream)) != FTWA_OK) return st;
+    const int64_t every = p.record_every;
+    for (int64_t r = 0, step = 0; step < p.n_steps || r == 0; ++r, step += every) {
+        if (r > 0) {
+            TableChunk t;
+            t.n = 1;
+            t.e[0] = e;
+            t.e[0].X = e.X + r * 2 * e.N * e.Mc;
+            if (e.v_env) t.e[0].v_env = e.v_env + 2 * step;
+            hipLaunchKernelGGL(write_table_kernel, dim3(1), dim3(256), 0, stream,
+                               reinterpret_cast<ResidentInst*>(ws + p.r_table) + Ld.first_entry, t);
+            FTWA_LAUNCH_CHECK("write_table_kernel");
+        }
+        L.n_steps = std::min(every, p.n_steps - step);
+        if ((st = timer.begin(stream)) != FTWA_OK) return st;
+        if ((st = resident_launch(L, stream)) != FTWA_OK) return st;
+        if ((st = timer.end(stream, 1, (double)e.Mc * L.n_steps)) != FTWA_OK) return st;
+        if (L.n_steps == every &&
+            (st = record_inv(c, tab, p.dtype, parts + (r + 1) * 4 * e.Mc, stream)) != FTWA_OK)
+            return st;
+    }
     return FTWA_OK;
 }
 
@@ -597,6 +647,12 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
             L.potential = Ld.potential;
             L.hopping = Ld.hopping;
             L.interaction = Ld.interaction;
+            if (g.by_record) {
+                if ((st = launch_by_record(p, inst[g.members[0]], g.members[0], Ld, L, ws, stream,
+                                           timer)) != FTWA_OK)
+                    return st;
+                continue;
+            }
             if ((st = timer.begin(stream)) != FTWA_OK) return st;
             if ((st = resident_launch(L, stream)) != FTWA_OK) return st;
             if ((st = timer.end(stream, 1, Ld.work)) != FTWA_OK) return st;
@@ -866,6 +922,11 @@ ftwa_status ftwa_evolve_static(const ftwa_instance* inst, int n_inst, double dt,
         return fail(FTWA_EINVAL, "ftwa_evolve_static: kernel timing is not available");
     Plan plan;
     if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan)) != FTWA_OK)
+        return st;
+    // the split kernel's mailboxes are larger than a few trajectories' stream chunks
+    if (plan.total > kStaticScratchBytes &&
+        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, false)) !=
+            FTWA_OK)
         return st;
     if (plan.total > kStaticScratchBytes)
         return fail(FTWA_EINVAL, "ftwa_evolve_static: this run needs " + std::to_string(plan.total) +
