@@ -29,7 +29,7 @@ const Config* const kConfigTable[] = {
     &kConfigsF64Shared[10], &kConfigsF32Shared[8], &kConfigsF64Shared[11],
     &kConfigsF32Shared[9], &kConfigsF64Shared[12], &kConfigsF32Shared[10],
     &kConfigsF64Shared[13], &kConfigsF32Shared[11], &kConfigsF64Shared[14],
-    &kConfigsF32Shared[12]
+    &kConfigsF32Shared[12], &kConfigsF64Split[4]
 };
 constexpr int kNumConfigs = (int)(sizeof(kConfigTable) / sizeof(kConfigTable[0]));
 inline const Config& config_at(int k) { return *kConfigTable[k]; }
@@ -39,7 +39,7 @@ inline const Config& config_at(int k) { return *kConfigTable[k]; }
 // those of kConfigTable).
 const int kPreference[] = {31, 29, 27, 25, 0, 33, 13, 1, 23, 24, 35, 14, 2, 15, 3,
                            32, 30, 28, 26, 4, 34, 16, 5, 36, 17, 6, 18, 7,
-                           8, 9, 10, 11, 12, 22, 19, 20, 21};
+                           8, 9, 10, 11, 12, 37, 19, 22, 20, 21};
 static_assert(sizeof(kPreference) == sizeof(kConfigTable) / sizeof(kConfigTable[0]) * sizeof(int),
               "every configuration has a place in the preference order");
 
@@ -65,10 +65,12 @@ size_t split_lds_bytes(const Config& c, int max_slots) {
     return (b + 15) / 16 * 16 + lds_tail(c);
 }
 // Published words per element of the split kernel, and per group of 2G
-// workgroups: [2 spins][G parts][2 parities][entries][words].
+// workgroups: [2 spins][G parts][2 parities][entries][words], then its
+// flags and the members' XCDs.
 int64_t split_words(const Config& c) {
-    const int64_t w = c.dtype == FTWA_F64 ? 4 : 2;
-    return 2 * (int64_t)c.G * 2 * (int64_t)c.NTU * (c.UE + c.UO) * w;
+    const int64_t w = c.dtype == FTWA_F64 ? 2 : 1;
+    const int64_t plane = (int64_t)c.NTU * (c.UE + c.UO) + kSplitPlanePad;
+    return 2 * (int64_t)c.G * 2 * plane * w + kSplitSyncWords;
 }
 
 }  // namespace
@@ -312,6 +314,10 @@ bool resident_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, ResidentPla
             if (need_interaction) lds += 3 * 256 * (c.dtype == FTWA_F64 ? 8 : 4);  // D, h copies
             else if (need_hop) lds += 256 * 6 * (c.dtype == FTWA_F64 ? 8 : 4);  // ratio table
             else if (need_potential) lds += 256 * (c.dtype == FTWA_F64 ? 8 : 4);  // the profile
+            // where the halo elements are published, a word each (the kernel
+            // reads that from global memory where LDS has no room for it)
+            const size_t imp = ((size_t)sh.max_halo * 4 + 15) / 16 * 16;
+            if (lds + imp <= kMaxLds) lds += imp;
         } else {
             if (P + 33 > 0x7fff) continue;
             if ((int64_t)c.NTU * c.UE < n_even || (int64_t)c.NTU * c.UO < n_odd) continue;

@@ -5,6 +5,9 @@
 
 namespace ftwa {
 
+// Pause between two looks at stale flags, in units of 64 cycles.
+constexpr int kSplitSleep = 4;
+
 // ---------------------------------------------------------------- split kernel
 // A spin block too large for one CU (the 198-site block in FP64: 315 KB)
 // spread over G workgroups ("parts") placed on one XCD: part p owns the stored
@@ -12,25 +15,44 @@ namespace ftwa {
 // element count) and keeps, besides its own elements, the "halo" its stencils
 // read from the neighbouring strips in LDS.  Every stage each part publishes
 // the next values of its exported elements (those another part reads, and
-// the diagonal, which the other spin's parts read for the U term) into a
-// per-part area of global memory, and copies in its halo and the partner
-// spin's diagonal.  Every published 32-bit word travels with the number of
-// the stage it belongs to in one 64-bit relaxed agent-scope atomic (two
-// areas alternating by stage parity), so no fences are needed; a word is
-// never overwritten before it is read because the stencil relation is
-// symmetric (a part that reads a neighbour's element is read back by it in
-// the other class) and the diagonal exchange is all-to-all, so no member of
-// a group runs two stages ahead of a reader.  Waits are bounded.
+// the diagonal, which the other spin's parts read for the U term) in a
+// per-part area of global memory (two areas alternating by stage parity) and
+// copies in its halo and the partner spin's diagonal.
+//
+// Every wave of every part has a flag per class: the last stage whose even
+// (odd) exports it has published.  It raises the flag a slot or more after
+// its last export, when the stores have reached the L2 anyway, and no barrier
+// is spent on it.  A reader looks at the flags of all members (one load, a
+// flag per lane) a slot before it needs them, then reads the values, two
+// 8-byte words each in FP64, while it computes the following slots.  The XCD's
+// L2 is what the members share: they compare their XCDs once per launch, and
+// where all are one, published words stop at the L2 (`near`) instead of being
+// written through to memory.  Otherwise the stores, the fences and the loads
+// are those of the agent scope.
+//
+// No word is overwritten before it is read: a part publishes into an area
+// again two stages later, after it has waited there for the odd flags of all
+// parts of its spin for the stage between (by then these have landed both
+// halos of the area's stage) and before that for the even flags of all
+// members (the other spin's parts have then read the area's diagonal).
+// Waits are bounded.
 //
 // The two-phase stage stays, with the waits placed where their data has had
 // the most time to arrive: the even elements of a part are ordered interior
 // (they read no other part's element) before boundary (the diagonal and the
-// exported ones).  The reads of both halos of a stage's input are issued at
-// the start of the stage; the odd halo (published early in the producers'
-// previous phase 2: exported odd elements come first) is needed only from the
-// boundary slots on, after a barrier; the even halo (published in the
-// producers' previous phase 1) before phase 2; the partner's diagonal of the
-// next stage's input is read during phase 2.
+// exported ones), exported odd elements come first in theirs.  The odd halo
+// is read during the last interior slots and landed before the boundary ones;
+// the even halo of the next stage and the partner's diagonal are read during
+// the last odd slots and landed at the end of the stage.
+//
+// What bounds it: a stage's chain of element slots and exchanges, not the
+// ALUs (VALU busy about 40 %).  198 sites, 512 trajectories, 50 steps: 14.4 ms,
+// 1.78e6 trajectory-steps/s, 5.4 us a stage and group; 27.5 ms before, when
+// every 32-bit word carried its stage number and was written through to
+// memory (twice the bytes, four loads and stores an element, and a wait for
+// the stores' round trip at every descriptor behind them).  150 sites, 500
+// trajectories: 8.7 -> 7.2 ms.  Reading an element ahead spills (198 sites 17.7
+// ms, 150 sites 13.8 ms).
 
 // Sub-dword-select shifts with the shift as a template argument.
 template <int SH> __device__ __forceinline__ uint32_t lo16_shl(uint32_t w) {
@@ -95,10 +117,69 @@ __device__ __forceinline__ cplx_t<T> element_rhs_split(bool gen, bool xp, const 
                                                               t, U, own, Vd, Aw, pot_on, Wt);
 }
 
-// A complex value as 32-bit payload words and back.
+// What an element's right-hand side reads from LDS, all of it issued before
+// the first sum.
+template <typename T> struct ElemIn {
+    cplx_t<T> n[6], own;
+    T di, dj, vi, vj;
+};
+
+template <typename T, bool OWN, int SH, int DSH, bool POT>
+__device__ __forceinline__ void read_elem(ElemIn<T>& in, bool gen, bool xp, const unsigned char* Yb,
+                                          const unsigned char* Yd, const unsigned char* Vd,
+                                          const uint4& d) {
+    const Stencil e = gen ? decode_split<SH, DSH, true>(d, xp) : decode_split<SH, DSH, false>(d, xp);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        in.n[k] = gen ? lds_at<T>(Yb, e.n[k]) : *reinterpret_cast<const cplx_t<T>*>(Yb + e.n[k]);
+    in.di = *reinterpret_cast<const T*>(Yd + e.di);
+    in.dj = *reinterpret_cast<const T*>(Yd + e.dj);
+    if constexpr (OWN) in.own = *reinterpret_cast<const cplx_t<T>*>(Yb + e.own);
+    if constexpr (POT) {
+        in.vi = *reinterpret_cast<const T*>(Vd + e.di);
+        in.vj = *reinterpret_cast<const T*>(Vd + e.dj);
+    }
+}
+
+// element_rhs of those values (the same operations in the same order).
+template <typename T, bool T1, bool POT>
+__device__ __forceinline__ cplx_t<T> rhs_elem(const ElemIn<T>& in, bool gen, const uint4& d, T t, T U,
+                                              cplx_t<T> rho, T Aw, bool pot_on) {
+    using C = cplx_t<T>;
+    const C *c = in.n, *r = in.n + 3;
+    C col, row;
+    col.x = (c[0].x + c[1].x) + c[2].x;
+    row.x = (r[0].x + r[1].x) + r[2].x;
+    if (gen) {
+        const uint32_t f[6] = {d.x << 16, d.x, d.y << 16, d.y, d.z << 16, d.z};
+        T q[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) q[k] = conj_sign<T>(f[k]);
+        col.y = fma_rn<T>(q[2], c[2].y, fma_rn<T>(q[1], c[1].y, q[0] * c[0].y));
+        row.y = fma_rn<T>(q[5], r[2].y, fma_rn<T>(q[4], r[1].y, q[3] * r[0].y));
+    } else {
+        col.y = (c[0].y + c[1].y) + c[2].y;
+        row.y = (r[0].y + r[1].y) + r[2].y;
+    }
+    T a = U * (in.di - in.dj);
+    if constexpr (POT) {
+        if (pot_on) a = a + Aw * (in.vi - in.vj);
+    }
+    if constexpr (T1) {
+        C k;
+        const T gr = fma_rn<T>(a, rho.x, col.x - row.x);
+        const T gi = fma_rn<T>(a, rho.y, col.y - row.y);
+        k.x = -gi;
+        k.y = gr;
+        return k;
+    }
+    return rhs_element<T>(col, row, rho, t, a);
+}
+
+// A value as published 64-bit words and back.
 template <typename T> struct Payload {
-    static constexpr int W = (int)sizeof(cplx_t<T>) / 4;
-    uint32_t w[W];
+    static constexpr int W = (int)sizeof(cplx_t<T>) / 8;
+    uint64_t w[W];
 };
 template <typename T> __device__ __forceinline__ Payload<T> to_payload(cplx_t<T> v) {
     return __builtin_bit_cast(Payload<T>, v);
@@ -106,62 +187,63 @@ template <typename T> __device__ __forceinline__ Payload<T> to_payload(cplx_t<T>
 template <typename T> __device__ __forceinline__ cplx_t<T> from_payload(const Payload<T>& p) {
     return __builtin_bit_cast(cplx_t<T>, p);
 }
+// The real part from the first word.
+__device__ __forceinline__ void real_of(uint64_t w, double& x) { x = __longlong_as_double((long long)w); }
+__device__ __forceinline__ void real_of(uint64_t w, float& x) { x = __uint_as_float((uint32_t)w); }
 
-// Publishes a value: every payload word with the stage number in the high
-// half, each a relaxed agent-scope atomic (a reader sees the old or the new
-// stage of a word, never a mixture); word k at dst + k * stride (word-major
-// areas: the threads of a wave write consecutive words).
-template <typename T>
-__device__ __forceinline__ void publish(uint64_t* dst, int stride, cplx_t<T> v, uint32_t stamp) {
-    const Payload<T> p = to_payload<T>(v);
-#pragma unroll
-    for (int k = 0; k < Payload<T>::W; ++k)
-        __hip_atomic_store(dst + (size_t)k * stride, ((uint64_t)stamp << 32) | p.w[k],
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// A published word: a wave-uniform base, opaque so that it stays in scalar
+// registers, and a 32-bit byte offset; loads and stores take both as they are.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define FTWA_GLOBAL __attribute__((address_space(1)))
+#else
+#define FTWA_GLOBAL  // host pass of the kernel source only
+#endif
+template <typename V> __device__ __forceinline__ FTWA_GLOBAL V* published(V* base, uint32_t at) {
+    uint64_t b = uniform64((uint64_t)base);
+    __asm__("" : "+s"(b));
+    return (FTWA_GLOBAL V*)(b + at);
+}
+template <typename V> __device__ __forceinline__ V peek(V* base, uint32_t at) {
+    return __hip_atomic_load(published(base, at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// `near`: every workgroup of the group runs on this XCD, so the word need go
+// no further than the L2 they share (a round trip between two workgroups
+// takes 0.6 of the one through memory).
+template <typename V>
+__device__ __forceinline__ void poke(V* base, uint32_t at, V v, bool near) {
+    if (near)
+        __hip_atomic_store(published(base, at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+        __hip_atomic_store(published(base, at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint64_t peek(const uint64_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// The XCD this wave runs on.
+__device__ __forceinline__ uint32_t xcc_id() {
+    uint32_t v;
+    __asm__ volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
+    return v & 15u;
 }
 
-// Waits until NW published words carry stage `want`: w[k] was read from
-// src[k / WPE] + (k % WPE) * stride (WPE = NW / NP, null pointers are
-// skipped); while any word is stale, all of them are read again (one round
-// trip per retry).
-// Bounded: false (abort flag and error word set) when the stage never comes
-// or another wait of the workgroup gave up.
-template <int NW, int NP>
-__device__ __forceinline__ bool settle_words(const uint64_t* const* src, int stride, uint64_t* w,
-                                             uint32_t want, int& abort_flag, int* error,
-                                             unsigned limit) {
-    constexpr int WPE = NW / NP;
-    unsigned it = 0;
-    while (true) {
-        bool ok = true;
-#pragma unroll
-        for (int k = 0; k < NW; ++k)
-            ok = ok && (src[k / WPE] == nullptr || (uint32_t)(w[k] >> 32) == want);
-        if (ok) return true;
-        if (*reinterpret_cast<volatile int*>(&abort_flag)) return false;
-        if (++it >= limit) {
-            abort_flag = 1;
-            atomicExch(error, 1);
-            return false;
-        }
-        // ~2000 cycles: polling less often leaves the memory system to the
-        // producers (a shorter sleep is slower overall)
-        __builtin_amdgcn_s_sleep(32);
-#pragma unroll
-        for (int k = 0; k < NW; ++k)
-            if (src[k / WPE]) w[k] = peek(src[k / WPE] + (size_t)(k % WPE) * stride);
-    }
+// Whether the 2G workgroups of a group run on one XCD, whose L2 they then
+// share: each leaves its XCD in a word (zero before the launch) and reads the
+// others'.  Bounded: a member that does not come counts as elsewhere.
+template <int G>
+__device__ __forceinline__ bool same_xcd(uint64_t* ids, int member, unsigned limit) {
+    const uint32_t mine = xcc_id();
+    const int lane = (int)(threadIdx.x & 63);
+    if (threadIdx.x == 0)
+        __hip_atomic_store(ids + member, (1ull << 32) | mine, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t w = lane < 2 * G ? 0 : (1ull << 32) | mine;
+    for (unsigned it = 0; w == 0 && it < limit; ++it) w = peek(ids, (uint32_t)lane * 8u);
+    return __all(w == ((1ull << 32) | mine));
 }
 
 // T1: every instance of the launch has t = 1.  Even slots: interior elements
 // in u < UB (the first GE1 slots read transposes), boundary elements from UB
 // (the diagonal first; slots UB .. UB + GE2 - 1 read transposes); odd slots:
 // the first GO read transposes, exported elements in the first XO.  KB: halo
-// entries per thread whose reads are issued a phase ahead.  POT: entries may
+// entries per thread and class whose reads are in flight at once.  POT: entries may
 // carry an external potential (its profile after the two diagonal copies, in
 // their layout; the element slots follow it).  GINT: every entry carries a
 // general interaction u_ij (ResidentInst::umat, as the spin-split kernels
@@ -180,8 +262,10 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     constexpr int SH = CB == 8 ? 3 : 4;   // slot number -> byte offset
     constexpr int DSH = TB == 4 ? 2 : 3;  // diagonal position -> byte offset
     constexpr int W = Payload<T>::W;      // published words per element
-    constexpr int DW = TB / 4;            // words of the real part
+    constexpr int NW = NTU / 64;          // waves
     constexpr int kEnt = NTU * (UE + UO); // descriptor entries of a part
+    constexpr int kPlane = kEnt + kSplitPlanePad;  // published words of one kind (the first
+                                                   // after kEnt takes what nobody reads)
     constexpr int kEvenPad = NTU * UE;
     constexpr uint32_t kDiagCopy = 256 * TB;
     static_assert(GE1 <= UB && UB < UE && UB + GE2 <= UE && GO <= UO && XO <= UO,
@@ -201,11 +285,18 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     const int group = (k / (2 * G)) * 8 + xcd;
     const int64_t n_groups = gridDim.x / (2 * G);
     if (tid0 == 0) *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8)) = 0;
-    // published words of this group: [2 spins][G parts][2 parities][W][kEnt]
-    uint64_t* const xg = A.mailbox + (size_t)group * 2 * G * 2 * kEnt * W;
-    auto xslot = [&](int spin, int q, uint32_t stamp) {
-        return xg + ((size_t)(spin * G + q) * 2 + (stamp & 1)) * kEnt * W;
+    // published words of this group: [2 spins][G parts][2 parities][W][kPlane],
+    // the stage every wave of every member has published its even and its
+    // odd elements of, then every member's XCD; a byte offset holds a member's
+    // area and element (parity 0)
+    static_assert(2 * G * NW <= 64, "a flag per lane");
+    uint64_t* const xg = A.mailbox + (size_t)group * (2 * G * 2 * kPlane * W + kSplitSyncWords);
+    uint32_t* const flags = reinterpret_cast<uint32_t*>(xg + (size_t)2 * G * 2 * kPlane * W);
+    auto xbase = [&](uint32_t stamp) { return xg + (size_t)(stamp & 1) * kPlane * W; };
+    auto xword = [&](int spin, uint32_t qs) {
+        return ((uint32_t)((spin * G + (int)(qs >> 16)) * 2 * kPlane * W) + (qs & 0xffffu)) * 8u;
     };
+    const bool near = same_xcd<G>(xg + (size_t)2 * G * 2 * kPlane * W + 64, member, A.spin_limit);
     int64_t g = 0;  // stage counter (continues across items)
 
     C y[UE + UO], acc[UE + UO], hold[UE];
@@ -237,9 +328,16 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
         // h_k = d_k + 1/2, zero from N up to the u table's row count (GINT),
         // then the part's elements; HOP: the stage's ratio table (256 places)
         // in place of those
-        unsigned char* const Yb =
-            lds_ptr(HOP ? 2 * kDiagCopy + 256 * 6 * TB : (GINT ? 5 : POT ? 3 : 2) * kDiagCopy);
+        constexpr uint32_t kYb = HOP ? 2 * kDiagCopy + 256 * 6 * TB : (GINT ? 5 : POT ? 3 : 2) * kDiagCopy;
+        unsigned char* const Yb = lds_ptr(kYb);
         unsigned char* const dpart = lds_ptr(0);
+        // byte offsets at which the halo elements are published: in LDS where
+        // it has room for them (a stage's first reads then wait for no other
+        // load), else formed from the table in global memory
+        const uint32_t imp_at = kYb + (uint32_t)(n_own + n_ie + n_io + 33) * CB;
+        uint32_t* const himp = reinterpret_cast<uint32_t*>(lds_ptr(imp_at));
+        const bool imp_lds = imp_at + (uint32_t)(n_ie + n_io) * 4u <= A.tail_off;
+        auto import_at = [&](int h) { return imp_lds ? himp[h] : xword(spin0, imp[h]); };
         auto hsite = [&](int c) { return reinterpret_cast<T*>(lds_ptr((3 + c) * kDiagCopy)); };
         int& abort_flag = *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8));
         const int64_t Mc = E.Mc;
@@ -291,7 +389,11 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
             const uint32_t qs = imp[h];
             const uint32_t* const pq = blob + (size_t)(qs >> 16) * pw + 8 + 4 * kEnt;
             reinterpret_cast<C*>(Yb)[n_own + h] = load_elem(pq[qs & 0xffffu]);
+            if (imp_lds) himp[h] = xword(spin0, qs);
         }
+        // this thread's site of the partner's diagonal: where it is published,
+        // and its position
+        const uint32_t dia_w = t < N ? xword(1 - spin0, dsrc[t]) : 0u;
         if (t < 33) {
             C z;
             z.x = 0;
@@ -349,45 +451,70 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
         const T c_sixth = uniform_real<T>((T)(A.dt / 6.0));
         bool first = true;  // the item's first stage: its halo came from HBM
 
-        // Halo copies: the reads of this thread's first KB entries of [h0, h1)
-        // are issued early (issue), the values land in their slots later
-        // (land; further entries, if any, are read there).
-        struct Batch {
-            uint64_t w[KB * W];
-            const uint64_t* src[KB];
+        // This wave has published its elements of class CLS for stage `stamp`:
+        // its stores are in the L2 (in memory, where the group is not near).
+        auto signal = [&](int cls, uint32_t stamp) {
+            if (near) __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if ((t & 63) == 0) poke(flags, (uint32_t)(cls * 64 + member * NW + t / 64) * 4u, stamp, near);
         };
-        auto issue = [&](Batch& bt, int h0, int h1, uint32_t want) {
+        // The flags of a class: of every member (even: the halo and the
+        // partner's diagonal), of the members of this spin (odd).
+        auto look = [&](int cls) { return peek(flags, (uint32_t)(cls * 64 + (t & 63)) * 4u); };
+        auto await = [&](int cls, uint32_t seen, uint32_t want) {
+            const int l = t & 63;
+            const bool mine = cls == 0 ? l < 2 * G * NW
+                                       : l >= spin0 * G * NW && l < (spin0 + 1) * G * NW;
+            unsigned it = 0;
+            while (!__all(!mine || (int32_t)(seen - want) >= 0)) {
+                if (*reinterpret_cast<volatile int*>(&abort_flag)) break;
+                if (++it >= A.spin_limit) {
+                    abort_flag = 1;
+                    if (l == 0) atomicExch(A.error, 1);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(kSplitSleep);
+                seen = look(cls);
+            }
+            if (near) __asm__ volatile("" ::: "memory");
+            else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        };
+
+        // Halo copies: KB entries of [h0, h1) per thread at a time, read and
+        // landed in their slots (further ones, if any, one after another).
+        struct Batch {
+            uint64_t w[KB][W];
+        };
+        auto fetch = [&](Batch& bt, int h0, int h1, uint32_t want) {
 #pragma unroll
             for (int j = 0; j < KB; ++j) {
                 const int h = h0 + t + j * NTU;
-                bt.src[j] = nullptr;
                 if (h < h1) {
-                    const uint32_t qs = imp[h];
-                    bt.src[j] = xslot(spin0, (int)(qs >> 16), want) + (qs & 0xffffu);
+                    const uint32_t at = import_at(h);
 #pragma unroll
-                    for (int kk = 0; kk < W; ++kk) bt.w[j * W + kk] = peek(bt.src[j] + (size_t)kk * kEnt);
+                    for (int kk = 0; kk < W; ++kk)
+                        bt.w[j][kk] = peek(xbase(want) + (size_t)kk * kPlane, at);
                 }
             }
         };
         auto land = [&](Batch& bt, int h0, int h1, uint32_t want) {
-            for (int hb = h0;; ) {
-                if (!settle_words<KB * W, KB>(bt.src, kEnt, bt.w, want, abort_flag, A.error,
-                                              A.spin_limit))
-                    return;
+            for (;;) {
 #pragma unroll
                 for (int j = 0; j < KB; ++j) {
-                    if (bt.src[j]) {
+                    const int h = h0 + t + j * NTU;
+                    if (h < h1) {
                         Payload<T> pl;
 #pragma unroll
-                        for (int kk = 0; kk < W; ++kk) pl.w[kk] = (uint32_t)bt.w[j * W + kk];
-                        reinterpret_cast<C*>(Yb)[n_own + hb + t + j * NTU] = from_payload<T>(pl);
+                        for (int kk = 0; kk < W; ++kk) pl.w[kk] = bt.w[j][kk];
+                        reinterpret_cast<C*>(Yb)[n_own + h] = from_payload<T>(pl);
                     }
                 }
-                hb += KB * NTU;
-                if (hb >= h1) return;
-                issue(bt, hb, h1, want);
+                h0 += KB * NTU;
+                if (h0 >= h1) return;
+                fetch(bt, h0, h1, want);
             }
         };
+        Batch be;  // the even halo of the next stage's input
 
         auto run_stage = [&](auto stage_tag) -> bool {
             constexpr int STAGE = decltype(stage_tag)::value;
@@ -458,89 +585,132 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
                 Uu = (T)1;
             }
             const uint32_t stamp = (uint32_t)(g + 1);
-            uint64_t* const mine = xslot(spin0, part, stamp);
+            uint64_t* const mine = xbase(stamp) + (size_t)(spin0 * G + part) * 2 * kPlane * W;
             desc = launder(desc);
             const __amdgpu_buffer_rsrc_t drs = __builtin_amdgcn_make_buffer_rsrc(
                 (void*)desc, (short)0, (int)(kEnt * 16), 0x00020000);
-            constexpr int KP = 2;
+            constexpr int KP = 3;  // descriptors in flight (2: 6 % slower)
             auto entry_of = [](int v) { return v < UE ? NTU * v : kEvenPad + NTU * (v - UE); };
             uint4 dq[KP];
 #pragma unroll
-            for (int v = 0; v < KP; ++v) dq[v] = slot_desc_buf<uint4>(drs, entry_of(v < UE + UO ? v : UE + UO - 1), toff);
-            // the halo of this stage's input (published in the producers'
-            // previous stage): reads issued now, landed before the elements
-            // that need them (the odd halo before the boundary, the even halo
-            // before phase 2)
-            Batch bo, be;
-            if (!first) {
-                issue(bo, n_ie, n_ie + n_io, (uint32_t)g);
-                issue(be, 0, n_ie, (uint32_t)g);
-            }
+            for (int v = 0; v < KP - 1; ++v) dq[v] = slot_desc_buf<uint4>(drs, entry_of(v), toff);
+            auto next_desc = [&](int u) {
+                if (u + KP - 1 < UE + UO)
+                    dq[(u + KP - 1) % KP] = slot_desc_buf<uint4>(drs, entry_of(u + KP - 1), toff);
+            };
+            auto is_gen = [](int u) {
+                return u < UE ? u < GE1 || (u >= UB && u < UB + GE2) : u - UE < GO;
+            };
+            auto is_xp = [](int u) { return u < UE ? u >= UB : u - UE < XO; };
+            ElemIn<T> in;
+            auto read = [&](int u) {
+                if constexpr (!HOP) {
+                    const uint4& d = dq[u % KP];
+                    if (u >= UE && STAGE > 1)
+                        read_elem<T, true, SH, DSH, POT>(in, is_gen(u), is_xp(u), Yb, Ud, vpart, d);
+                    else
+                        read_elem<T, false, SH, DSH, POT>(in, is_gen(u), is_xp(u), Yb, Ud, vpart, d);
+                }
+            };
+            // every lane of an exporting slot stores (what is not exported to
+            // the spare word), so the loads around it keep exact wait counts
+            auto export_elem = [&](const uint4& d, C v) {
+                const Payload<T> p = to_payload<T>(v);
+                const uint32_t at = d.w & 0x8000u ? (d.w & 0x7fffu) * 8u : (uint32_t)kEnt * 8u;
+                if (near) {
+#pragma unroll
+                    for (int k = 0; k < W; ++k) poke(mine + (size_t)k * kPlane, at, p.w[k], true);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < W; ++k) poke(mine + (size_t)k * kPlane, at, p.w[k], false);
+                }
+            };
+            Batch bo;
+            uint32_t fl = 0;
+            if (!first) land(be, 0, n_ie, (uint32_t)g);
             // ---------------- phase 1: even elements (next values held)
 #pragma unroll
             for (int u = 0; u < UE; ++u) {
+                constexpr int UL = UB > 2 ? UB - 2 : 1;
+                if (u == UL - 1) fl = look(1);
+                if (u == UL && u < UB) {
+                    // (also in an item's first stage: no member overwrites
+                    // what another has still to read)
+                    await(1, fl, (uint32_t)g);
+                    if (!first) fetch(bo, n_ie, n_ie + n_io, (uint32_t)g);
+                }
                 if (u == UB) {
                     // the boundary elements read the odd halo
                     if (!first) land(bo, n_ie, n_ie + n_io, (uint32_t)g);
                     __syncthreads();
                 }
+                next_desc(u);
                 const uint4 d = dq[u % KP];
-                if (u + KP < UE + UO) dq[u % KP] = slot_desc_buf<uint4>(drs, entry_of(u + KP), toff);
                 const C own = STAGE == 1 ? y[u] : hold[u];
-                const bool xp = u >= UB;
-                const bool gen = u < GE1 || (u >= UB && u < UB + GE2);
+                const bool xp = is_xp(u);
                 const uint32_t ob = xp ? (d.w & 0x7fffu) << SH : lo16_shl<SH>(d.w);
                 *reinterpret_cast<C*>(Yb + ob) = own;
-                const C kk = element_rhs_split<T, true, T1, SH, DSH, POT, HOP>(
-                    gen, xp, Yb, Ud, d, tw, Uu, own, vpart, Aw, pot_on, Wt);
+                read(u);
+                __builtin_amdgcn_sched_barrier(0);
+                C kk;
+                if constexpr (HOP)
+                    kk = element_rhs_split<T, true, T1, SH, DSH, POT, HOP>(
+                        is_gen(u), xp, Yb, Ud, d, tw, Uu, own, vpart, Aw, pot_on, Wt);
+                else
+                    kk = rhs_elem<T, T1, POT>(in, is_gen(u), d, tw, Uu, own, Aw, pot_on);
                 hold[u] = rk_update<STAGE, T>(c, kk, y[u], acc[u]);
                 pin(hold[u]);
                 pin(acc[u]);
                 if constexpr (STAGE == 4) pin(y[u]);
-                if (xp && (d.w & 0x8000u))
-                    publish<T>(mine + (d.w & 0x7fffu), kEnt, hold[u], stamp);
+                if (xp) export_elem(d, hold[u]);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // phase 2 reads the even halo
-            if (!first) land(be, 0, n_ie, (uint32_t)g);
             __syncthreads();
             // ---------------- phase 2: odd elements (written straight to LDS);
             // the partner's diagonal of the next stage's input is read
             // meanwhile (into the copy this stage does not read)
-            const uint64_t* dsrcp[1] = {nullptr};
-            uint64_t dw[DW];
-            if (t < N) {
-                const uint32_t qs = dsrc[t];
-                dsrcp[0] = xslot(1 - spin0, (int)(qs >> 16), stamp) + (qs & 0xffffu);
-#pragma unroll
-                for (int kk = 0; kk < DW; ++kk) dw[kk] = peek(dsrcp[0] + (size_t)kk * kEnt);
-            }
+            uint64_t dw = 0;
 #pragma unroll
             for (int u = UE; u < UE + UO; ++u) {
+                if (u == UE + 1) signal(0, stamp);
+                if (u == UE + XO + 1) signal(1, stamp);
+                if (u == UE + UO - 3) fl = look(0);
+                if (u == UE + UO - 2) {
+                    // every member is past its phase 1: the partner's diagonal
+                    // and the even halo of the next stage's input
+                    await(0, fl, stamp);
+                    if (t < N) dw = peek(xbase(stamp), dia_w);
+                    fetch(be, 0, n_ie, stamp);
+                }
+                next_desc(u);
                 const uint4 d = dq[u % KP];
-                if (u + KP < UE + UO) dq[u % KP] = slot_desc_buf<uint4>(drs, entry_of(u + KP), toff);
-                const bool xp = u - UE < XO;
-                const bool gen = u - UE < GO;
-                const C kk = STAGE == 1
-                    ? element_rhs_split<T, true, T1, SH, DSH, POT, HOP>(gen, xp, Yb, Ud, d, tw, Uu,
-                                                                        y[u], vpart, Aw, pot_on, Wt)
-                    : element_rhs_split<T, false, T1, SH, DSH, POT, HOP>(gen, xp, Yb, Ud, d, tw, Uu,
-                                                                         y[u], vpart, Aw, pot_on, Wt);
+                const bool xp = is_xp(u);
+                read(u);
+                __builtin_amdgcn_sched_barrier(0);
+                C kk;
+                if constexpr (HOP)
+                    kk = STAGE == 1
+                        ? element_rhs_split<T, true, T1, SH, DSH, POT, HOP>(
+                              is_gen(u), xp, Yb, Ud, d, tw, Uu, y[u], vpart, Aw, pot_on, Wt)
+                        : element_rhs_split<T, false, T1, SH, DSH, POT, HOP>(
+                              is_gen(u), xp, Yb, Ud, d, tw, Uu, y[u], vpart, Aw, pot_on, Wt);
+                else
+                    kk = rhs_elem<T, T1, POT>(in, is_gen(u), d, tw, Uu,
+                                              STAGE == 1 ? y[u] : in.own, Aw, pot_on);
                 const C nx = rk_update<STAGE, T>(c, kk, y[u], acc[u]);
                 const uint32_t ob = xp ? (d.w & 0x7fffu) << SH : lo16_shl<SH>(d.w);
                 *reinterpret_cast<C*>(Yb + ob) = nx;
                 pin(acc[u]);
                 if constexpr (STAGE == 4) pin(y[u]);
-                if (xp && (d.w & 0x8000u)) publish<T>(mine + (d.w & 0x7fffu), kEnt, nx, stamp);
+                if (xp) export_elem(d, nx);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (t < N && settle_words<DW, 1>(dsrcp, kEnt, dw, stamp, abort_flag, A.error,
-                                             A.spin_limit)) {
-                Payload<T> pl;
-#pragma unroll
-                for (int kk = 0; kk < W; ++kk) pl.w[kk] = kk < DW ? (uint32_t)dw[kk] : 0u;
-                reinterpret_cast<T*>(dpart + (STAGE & 1) * kDiagCopy)[dpos[t]] = from_payload<T>(pl).x;
-                if constexpr (GINT) hsite(STAGE & 1)[t] = from_payload<T>(pl).x + (T)0.5;
+            if constexpr (XO + 1 >= UO) signal(1, stamp);
+            if (t < N) {
+                T x;
+                real_of(dw, x);
+                reinterpret_cast<T*>(dpart + (STAGE & 1) * kDiagCopy)[dpos[t]] = x;
+                if constexpr (GINT) hsite(STAGE & 1)[t] = x + (T)0.5;
             }
             __syncthreads();
             ++g;

@@ -11,7 +11,7 @@ from tests._util import pack, unpack
 
 pytestmark = pytest.mark.gpu
 
-FIRST_SHARED = 37  # six FP64 shapes, then six FP32 shapes
+FIRST_SHARED = 38  # six FP64 shapes, then six FP32 shapes
 DT, STEPS, EVERY = 0.01, 6, 3
 
 
