@@ -41,15 +41,6 @@ constexpr int64_t kStreamChunk = 4096;
 constexpr size_t kStatusBytes = 256;
 constexpr uint32_t kStatusMagic = 0x46545741u;
 
-__global__ void status_init_kernel(uint32_t* st) {
-    if (threadIdx.x == 0) {
-        st[0] = kStatusMagic;
-        st[1] = 0u;
-        st[2] = 0u;
-        st[3] = 0xffffffffu;
-    }
-}
-
 __global__ __launch_bounds__(64) void status_nonfinite_kernel(const double* __restrict__ inv,
                                                               int64_t n_rec, uint32_t inst,
                                                               uint32_t* st) {
@@ -70,11 +61,46 @@ struct TableChunk {
 static_assert(sizeof(ResidentInst) % 4 == 0, "table entries are copied as 32-bit words");
 static_assert(sizeof(TableChunk) <= 3072, "kernel argument size");
 
-__global__ __launch_bounds__(256) void write_table_kernel(ResidentInst* dst, TableChunk c) {
+__device__ __forceinline__ void write_table(ResidentInst* dst, const TableChunk& c) {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(c.e);
     uint32_t* out = reinterpret_cast<uint32_t*>(dst);
     const int words = c.n * (int)(sizeof(ResidentInst) / 4);
     for (int w = threadIdx.x; w < words; w += blockDim.x) out[w] = src[w];
+}
+__global__ __launch_bounds__(256) void write_table_kernel(ResidentInst* dst, TableChunk c) {
+    write_table(dst, c);
+}
+
+// What a run needs before its first kernel, in one launch (a launch each took
+// 5 us of a 10-site run's 140): the status block, launch-table entries and the
+// cleared moments.  More than fit go into further launches.
+constexpr int kPrologueFills = 24;
+struct Prologue {
+    uint32_t* status;     // NULL: not in this launch
+    ResidentInst* table;  // c.n entries from here
+    int n_fill;
+    struct {
+        double* p;
+        int64_t n;
+    } fill[kPrologueFills];
+    TableChunk c;
+};
+static_assert(sizeof(Prologue) <= 4000, "kernel argument size");
+
+__global__ __launch_bounds__(256) void prologue_kernel(Prologue a) {
+    if (blockIdx.x == 0) {
+        if (a.status && threadIdx.x == 0) {
+            a.status[0] = kStatusMagic;
+            a.status[1] = 0u;
+            a.status[2] = 0u;
+            a.status[3] = 0xffffffffu;
+        }
+        write_table(a.table, a.c);
+    }
+    for (int k = 0; k < a.n_fill; ++k)
+        for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < a.fill[k].n;
+             e += (int64_t)gridDim.x * 256)
+            a.fill[k].p[e] = 0.0;
 }
 
 struct InstPlan {
@@ -519,23 +545,43 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
                     KernelTimer& timer, bool cooperative) {
     ftwa_status st;
     uint32_t* status = reinterpret_cast<uint32_t*>(ws + p.off_status);
-    hipLaunchKernelGGL(status_init_kernel, dim3(1), dim3(64), 0, stream, status);
-    FTWA_LAUNCH_CHECK("status_init_kernel");
-    for (size_t e0 = 0; e0 < p.table.size(); e0 += kTableChunk) {
-        TableChunk c;
-        c.n = (int)std::min<size_t>(kTableChunk, p.table.size() - e0);
-        std::memcpy(c.e, p.table.data() + e0, (size_t)c.n * sizeof(ResidentInst));
-        hipLaunchKernelGGL(write_table_kernel, dim3(1), dim3(256), 0, stream,
-                           reinterpret_cast<ResidentInst*>(ws + p.r_table) + e0, c);
-        FTWA_LAUNCH_CHECK("write_table_kernel");
-    }
+    Prologue pro;
+    pro.status = status;
+    size_t e0 = 0;
+    int64_t longest = 0;
+    auto flush = [&]() -> ftwa_status {
+        const size_t left = p.table.size() - e0;
+        pro.table = reinterpret_cast<ResidentInst*>(ws + p.r_table) + e0;
+        pro.c.n = (int)std::min<size_t>(kTableChunk, left);
+        if (pro.c.n) std::memcpy(pro.c.e, p.table.data() + e0, (size_t)pro.c.n * sizeof(ResidentInst));
+        const int64_t blocks = std::min<int64_t>(std::max<int64_t>((longest + 1023) / 1024, 1), 1024);
+        hipLaunchKernelGGL(prologue_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, pro);
+        FTWA_LAUNCH_CHECK("prologue_kernel");
+        e0 += (size_t)pro.c.n;
+        pro.status = nullptr;
+        pro.n_fill = 0;
+        longest = 0;
+        return FTWA_OK;
+    };
+    pro.n_fill = 0;
+    auto clear = [&](double* d, int64_t n) -> ftwa_status {
+        if (n <= 0) return FTWA_OK;
+        if (pro.n_fill == kPrologueFills && (st = flush()) != FTWA_OK) return st;
+        pro.fill[pro.n_fill].p = d;
+        pro.fill[pro.n_fill++].n = n;
+        longest = std::max(longest, n);
+        return FTWA_OK;
+    };
     for (int k = 0; k < p.n_inst; ++k) {
         const ftwa_instance& in = inst[k];
         const int D = 2 * in.lat->N;
-        if ((st = zero_fill(in.S1, p.n_rec * D, stream)) != FTWA_OK) return st;
-        if ((st = zero_fill(in.S2, p.n_rec * s2_count(D), stream)) != FTWA_OK) return st;
-        if (in.inv && (st = zero_fill(in.inv, p.n_rec * 4, stream)) != FTWA_OK) return st;
+        if ((st = clear(in.S1, p.n_rec * D)) != FTWA_OK) return st;
+        if ((st = clear(in.S2, p.n_rec * s2_count(D))) != FTWA_OK) return st;
+        if (in.inv && (st = clear(in.inv, p.n_rec * 4)) != FTWA_OK) return st;
     }
+    do {
+        if ((st = flush()) != FTWA_OK) return st;
+    } while (e0 < p.table.size());
     // ---- stream instances
     for (int k = 0; k < p.n_inst; ++k) {
         const InstPlan& ip = p.inst[k];

@@ -4,9 +4,12 @@
 //   S2[r][ab] += sum_m X[r][a][m] X[r][b][m]      (a <= b, packed)
 // X holds one chunk of trajectories, m innermost.  S2 is a symmetric rank-Mc
 // update: 32 x 32 output tiles, 2 x 2 outputs per thread, the trajectory
-// axis staged through LDS 64 at a time.  Each output is one FP64 fma chain
-// in ascending m within a split; splits are added in split order, so the
-// result is deterministic.
+// axis staged through LDS 64 at a time; the tiles on the diagonal sum their
+// rows for S1 on the way (in a kernel of its own S1 read all of X again: 152 us
+// beside S2's 748 at 10 sites, 100000 trajectories and 51 records).  Each S2
+// output is one FP64 fma chain in ascending m within a split, each S1 output 64
+// interleaved sums and a fixed butterfly; splits are added in split order, so the result is
+// deterministic.
 #include "ftwa_internal.h"
 
 namespace ftwa {
@@ -36,8 +39,7 @@ __global__ __launch_bounds__(256) void s2_partial_kernel(int D, int64_t Mc, int 
                                                          int64_t m_per_split,
                                                          const double* __restrict__ X,
                                                          double* __restrict__ out,
-                                                         int64_t out_rec_stride,
-                                                         int64_t out_split_stride,
+                                                         double* __restrict__ out1, int n_slot,
                                                          int accumulate) {
     __shared__ double xa[kTile][kMBlock + 1];
     __shared__ double xb[kTile][kMBlock + 1];
@@ -51,13 +53,18 @@ __global__ __launch_bounds__(256) void s2_partial_kernel(int D, int64_t Mc, int 
     const double* Xr = X + (int64_t)r * D * Mc;
     const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
     double acc[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+    double sum[kTile * kMBlock / 256] = {};  // of a row in every 64th trajectory
     for (int64_t m0 = m_lo; m0 < m_hi; m0 += kMBlock) {
         // stage 32 rows x 64 trajectories of each tile (zero beyond the ends)
-        for (int e = threadIdx.x; e < kTile * kMBlock; e += 256) {
-            const int row = e / kMBlock, col = e % kMBlock;
+#pragma unroll
+        for (int i = 0; i < kTile * kMBlock / 256; ++i) {
+            const int row = (int)threadIdx.x / kMBlock + i * (256 / kMBlock);
+            const int col = (int)threadIdx.x % kMBlock;
             const int64_t m = m0 + col;
             const int a = ta * kTile + row, b = tb * kTile + row;
-            xa[row][col] = (a < D && m < m_hi) ? Xr[(int64_t)a * Mc + m] : 0.0;
+            const double v = (a < D && m < m_hi) ? Xr[(int64_t)a * Mc + m] : 0.0;
+            xa[row][col] = v;
+            sum[i] += v;
             xb[row][col] = (b < D && m < m_hi) ? Xr[(int64_t)b * Mc + m] : 0.0;
         }
         __syncthreads();
@@ -75,39 +82,36 @@ __global__ __launch_bounds__(256) void s2_partial_kernel(int D, int64_t Mc, int 
         for (int v = 0; v < 2; ++v) {
             const int a = ta * kTile + ty + 16 * u, b = tb * kTile + tx + 16 * v;
             if (a >= D || b >= D || a > b) continue;
-            double* dst = out + (int64_t)r * out_rec_stride + (int64_t)split * out_split_stride +
+            double* dst = out + ((int64_t)r * n_slot + split) * ((int64_t)D * (D + 1) / 2) +
                           s2_index(a, b, D);
             *dst = accumulate ? *dst + acc[u][v] : acc[u][v];
         }
+    if (ta == tb)
+#pragma unroll
+        for (int i = 0; i < kTile * kMBlock / 256; ++i) {  // a wave holds a row
+            double s = sum[i];
+            for (int off = 32; off > 0; off /= 2) s += __shfl_xor(s, off, 64);
+            const int a = ta * kTile + (int)threadIdx.x / kMBlock + i * (256 / kMBlock);
+            if (threadIdx.x % kMBlock != 0 || a >= D) continue;
+            double* dst = out1 + ((int64_t)r * n_slot + split) * D + a;
+            *dst = accumulate ? *dst + s : s;
+        }
 }
 
-// S1 partial sums: one wave per (a, split, record), lanes stride m, then a
-// fixed butterfly over the wave.
-__global__ __launch_bounds__(64) void s1_partial_kernel(int D, int64_t Mc, int64_t m_per_split,
-                                                        const double* __restrict__ X,
-                                                        double* __restrict__ out,
-                                                        int64_t out_rec_stride,
-                                                        int64_t out_split_stride,
-                                                        int accumulate) {
-    const int a = blockIdx.x, split = blockIdx.y, r = blockIdx.z;
-    const int64_t m_lo = (int64_t)split * m_per_split;
-    const int64_t m_hi = m_lo + m_per_split < Mc ? m_lo + m_per_split : Mc;
-    const double* row = X + ((int64_t)r * D + a) * Mc;
-    double s = 0.0;
-    for (int64_t m = m_lo + threadIdx.x; m < m_hi; m += 64) s += row[m];
-    for (int off = 32; off > 0; off /= 2) s += __shfl_xor(s, off, 64);
-    if (threadIdx.x == 0) {
-        double* dst = out + (int64_t)r * out_rec_stride + (int64_t)split * out_split_stride + a;
-        *dst = accumulate ? *dst + s : s;
-    }
-}
-
-// S[r][k] += sum over splits (in order) of part[r][split][k]
-__global__ __launch_bounds__(256) void add_splits_kernel(int64_t count, int n_split,
-                                                         int64_t n_rec,
+// S[r][k] += sum over splits (in order) of part[r][split][k], for S2 then S1.
+__global__ __launch_bounds__(256) void add_splits_kernel(int64_t count2, int64_t count1,
+                                                         int n_split, int64_t n_rec,
                                                          const double* __restrict__ part,
-                                                         double* __restrict__ S) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                         double* __restrict__ S2,
+                                                         double* __restrict__ S1) {
+    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, count = count2;
+    double* S = S2;
+    if (e >= count2 * n_rec) {
+        e -= count2 * n_rec;
+        part += count2 * n_rec * n_split;
+        count = count1;
+        S = S1;
+    }
     if (e >= count * n_rec) return;
     const int64_t r = e / count, k = e - r * count;
     double s = part[(r * n_split) * count + k];
@@ -155,22 +159,16 @@ ftwa_status moments_accumulate(int D, int64_t Mc, int64_t n_rec, const double* X
     const int64_t n2 = s2_count(D);
     if (split_used == 1) {
         hipLaunchKernelGGL(s2_partial_kernel, dim3(pairs, 1, (unsigned)n_rec), dim3(256), 0, stream,
-                           D, Mc, 1, m_per, X, S2, n2, 0, 1);
-        hipLaunchKernelGGL(s1_partial_kernel, dim3(D, 1, (unsigned)n_rec), dim3(64), 0, stream, D,
-                           Mc, m_per, X, S1, (int64_t)D, 0, 1);
+                           D, Mc, 1, m_per, X, S2, S1, 1, 1);
         FTWA_LAUNCH_CHECK("moments (single split)");
         return FTWA_OK;
     }
     double* p2 = static_cast<double*>(scratch);
     double* p1 = p2 + (size_t)n_rec * split_used * n2;
     hipLaunchKernelGGL(s2_partial_kernel, dim3(pairs, split_used, (unsigned)n_rec), dim3(256), 0,
-                       stream, D, Mc, split_used, m_per, X, p2, n2 * split_used, n2, 0);
-    hipLaunchKernelGGL(s1_partial_kernel, dim3(D, split_used, (unsigned)n_rec), dim3(64), 0, stream,
-                       D, Mc, m_per, X, p1, (int64_t)D * split_used, (int64_t)D, 0);
-    hipLaunchKernelGGL(add_splits_kernel, dim3((unsigned)((n2 * n_rec + 255) / 256)), dim3(256), 0,
-                       stream, n2, split_used, n_rec, p2, S2);
-    hipLaunchKernelGGL(add_splits_kernel, dim3((unsigned)((D * n_rec + 255) / 256)), dim3(256), 0,
-                       stream, (int64_t)D, split_used, n_rec, p1, S1);
+                       stream, D, Mc, split_used, m_per, X, p2, p1, split_used, 0);
+    hipLaunchKernelGGL(add_splits_kernel, dim3((unsigned)(((n2 + D) * n_rec + 255) / 256)), dim3(256),
+                       0, stream, n2, (int64_t)D, split_used, n_rec, p2, S2, S1);
     FTWA_LAUNCH_CHECK("moments");
     return FTWA_OK;
 }
