@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cstring>
 #include <deque>
+#include <future>
 #include <map>
 #include <set>
 #include <unordered_map>
@@ -1088,7 +1089,7 @@ std::vector<uint32_t> shared_deal(const std::vector<SharedEntry>& all, size_t n_
         open_group();
         pick(diag, M, 0, diag.size());
         for (int limit = 1; limit <= 8; ++limit) pick(diag, per, limit, diag.size());
-        for (int limit = 0; limit <= 8; ++limit) pick(rest, M, limit, limit ? kWindow / 4 : kWindow);
+        for (int limit = 0; limit <= 8; ++limit) pick(rest, M, limit, kWindow);
         groups.push_back(g);
     }
     // the rest by shape (5 bits a neighbour) and own element, in the order in
@@ -1117,7 +1118,7 @@ std::vector<uint32_t> shared_deal(const std::vector<SharedEntry>& all, size_t n_
     std::sort(rest.begin(), rest.end());
     while (!rest.empty()) {
         open_group();
-        for (int limit = 0; limit <= 8; ++limit) pick(rest, M, limit, limit ? kWindow / 4 : kWindow);
+        for (int limit = 0; limit <= 8; ++limit) pick(rest, M, limit, kWindow);
         groups.push_back(g);
     }
     // within a group by own element, the two groups of 32 lanes a quarter
@@ -1165,27 +1166,35 @@ ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>
         head[lat->diag_pos[i]] = (uint32_t)i;
         head[N + lat->diag_pos[i]] = w;
     }
+    // One deal per class and lane count: the diagonal at the density that the
+    // shortest first pass needs.  They take 0.2 to 0.9 ms each at 54 sites, so
+    // they run side by side.
+    std::map<int, size_t> per;
+    for (const auto& [I, n_pass, n_list] : shapes) {
+        const size_t groups = (size_t)n_pass / (I >= 16 ? 1 : (size_t)(16 / I));
+        per[I] = std::max(per[I], ((size_t)N + groups - 1) / groups);
+    }
+    std::map<int, std::future<std::vector<uint32_t>>> dealing[2];
+    for (const auto& [I, density] : per)
+        for (int odd = 0; odd < 2; ++odd)
+            dealing[odd][I] = std::async(std::launch::async, [lat, N, odd, I = I, density = density] {
+                return shared_deal(shared_entries(*lat, odd != 0, I), odd ? 0 : (size_t)N, I,
+                                   density);
+            });
+    std::map<int, std::vector<uint32_t>> dealt[2];
+    for (int odd = 0; odd < 2; ++odd)
+        for (auto& [I, f] : dealing[odd]) dealt[odd][I] = f.get();
     std::map<std::array<int, 3>, size_t> at;
-    std::map<std::pair<int, size_t>, std::vector<uint32_t>> dealt[2];  // (I, per)
     std::vector<uint32_t> t;
     for (const auto& shape : shapes) {
-        if (at.count(shape)) continue;
-        const int I = shape[0];
-        const size_t n_pass = (size_t)shape[1], n_list = (size_t)shape[2];
-        at[shape] = t.size();
+        if (!at.emplace(shape, t.size()).second) continue;
         t.insert(t.end(), head.begin(), head.end());
-        // the diagonal within the first pass
-        const size_t M = I >= 16 ? 1 : (size_t)(16 / I);
-        const size_t per = ((size_t)N + n_pass / M - 1) / (n_pass / M);
         for (int odd = 0; odd < 2; ++odd) {
-            auto [d, fresh] = dealt[odd].try_emplace({I, odd ? 0 : per});
-            if (fresh)
-                d->second = shared_deal(shared_entries(*lat, odd != 0, I),
-                                        odd ? 0 : (size_t)N, I, per);
-            const size_t end = t.size() + n_list;
-            if (d->second.size() > n_list)
+            const std::vector<uint32_t>& list = dealt[odd][shape[0]];
+            const size_t end = t.size() + (size_t)shape[2];
+            if (list.size() > (size_t)shape[2])
                 return fail(FTWA_EINVAL, "shared-pack lists exceed their shape");
-            t.insert(t.end(), d->second.begin(), d->second.end());
+            t.insert(t.end(), list.begin(), list.end());
             t.resize(end, 0xffffffffu);
         }
     }
