@@ -805,16 +805,23 @@ ftwa_status evolve_stored(const ftwa_instance& in, double dt, int64_t n_steps, i
     std::memset(&tune, 0, sizeof(tune));
     tune.path = FTWA_PATH_RESIDENT;
     tune.resident_config = -1;
-    // These runs store the whole state at every record, so the shared-block
-    // tiles with several trajectories per workgroup come first (their stores
-    // of neighbouring trajectories share cache lines; the single-unit tiles
-    // that ordinary runs prefer took the 54-site checkpoint run from 0.24 to
-    // 0.38 s); otherwise the usual first fit (spin split, split kernel).
+    // Packs of small lattices first, as in ordinary runs (whole gradients, 1024
+    // trajectories, 200 steps: 54 sites FP32 stored every 50 steps 20.6 ms, on
+    // the tiles 21.8, every 5 steps 22.8 and 25.2; FP64 37.0 and 38.7, 39.7 and
+    // 42.0; 12 sites FP32 2.9 and 3.7, 3.2 and 4.5).  Then the shared-block
+    // tiles with several trajectories per workgroup (their stores of
+    // neighbouring trajectories share cache lines; the single-unit tiles that
+    // ordinary runs prefer took the 54-site checkpoint run from 0.24 to
+    // 0.38 s), then the usual first fit (spin split, split kernel).
     static const int kStoredPreference[] = {0, 13, 1, 23, 24, 14, 2, 15, 3,
                                             4, 16, 5, 17, 6, 18, 7};
     const DeviceTables& tab = host_tables(in.lat);
+    ResidentPlan rp;
+    const bool packs = !in.inv && shared_plan(in.lat->N, dtype, tab, in.n_traj, &rp, -1,
+                                              in.v_site != nullptr, in.hop_w != nullptr,
+                                              in.u_mat != nullptr);
     for (int c : kStoredPreference) {
-        ResidentPlan rp;
+        if (packs) break;
         if (resident_plan(in.lat->N, dtype, tab, &rp, c, in.inv == nullptr)) {
             tune.resident_config = c;
             break;
