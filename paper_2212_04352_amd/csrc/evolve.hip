@@ -121,6 +121,7 @@ struct LaunchDesc {                // one resident launch: a group in a pass
     int64_t n_items = 0;
     int64_t grid = 0;
     double work = 0;               // trajectory-steps
+    double share = 1;              // of the workgroups that the chip holds at once
     bool unit_hop = true;          // every instance has t = 1
     bool potential = false;        // an instance carries an external potential
     bool hopping = false;          // every instance carries complex hopping
@@ -136,6 +137,7 @@ struct GroupPlan {
     std::vector<int> members;
     int64_t max_items = 0;
     size_t off_mb = 0;
+    size_t off_mom = 0;            // scratch of its members' moments
 };
 
 struct Plan {
@@ -152,7 +154,7 @@ struct Plan {
     size_t s_acc = 0, s_ya = 0, s_yb = 0, s_x = 0, s_mom = 0, s_inv = 0, s_D = 0, s_total = 0;
     size_t off_status = 0;  // the status block (kStatusBytes at the start of the workspace)
     // resident area
-    size_t r_table = 0, r_mom = 0, r_total = 0;
+    size_t r_table = 0, r_total = 0;
     int64_t n_table = 0;
     size_t total = 0;
     // internal runs only (one instance): its state is stored at every record
@@ -171,9 +173,14 @@ void window(const Plan& p, const ftwa_instance& in, int k, int j, int64_t* m0, i
     *Mc = std::min<int64_t>(c, in.n_traj - *m0);
 }
 
+// Whether a configuration's workgroups run independently of each other.
+bool waits_for_none(int config) {
+    return resident_is_shared(config) || resident_spins(config) == 2;
+}
+
 ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_t n_steps,
                         int record_every, ftwa_dtype dtype, const ftwa_tuning* tune, Plan* out,
-                        bool allow_by_record = true) {
+                        bool compact = false) {
     if (dtype != FTWA_F64 && dtype != FTWA_F32) return fail(FTWA_EINVAL, "unknown dtype");
     if (n_steps < 0) return fail(FTWA_EINVAL, "n_steps < 0");
     if (record_every < 1) return fail(FTWA_EINVAL, "record_every < 1");
@@ -250,7 +257,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         // FP64, 500 trajectories, 50 steps, 6 records: 48.0 ms there, 11.3 ms
         // so; 20 steps with a record after each 21.1 and 13.8 ms, with 64
         // trajectories 3.9 and 3.9 ms).
-        if (!can_res && inst[k].inv && allow_by_record && force < 0 && want == FTWA_PATH_AUTO)
+        if (!can_res && inst[k].inv && !compact && force < 0 && want == FTWA_PATH_AUTO)
             can_res = ip.by_record = fits(true);
         // Small lattices whose shared-pack form fits (with the instance's
         // variant) run there; whether the resident path takes the instance at
@@ -376,12 +383,16 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             off = align_up(off + (size_t)p.n_rec * 4 * ip.chunk * sizeof(double));
         }
     }
-    size_t r_mom = 0;
-    for (int k = 0; k < n_inst; ++k)
-        if (p.inst[k].path == FTWA_PATH_RESIDENT)
-            r_mom = std::max(r_mom, moments_workspace_bytes(2 * inst[k].lat->N, p.inst[k].chunk,
-                                                            p.n_rec));
-    p.r_mom = off; off = align_up(off + r_mom);
+    size_t r_mom = 0;  // compact: one region for all groups
+    for (GroupPlan& g : p.groups) {
+        size_t need = 0;
+        for (int k : g.members)
+            need = std::max(need, moments_workspace_bytes(2 * inst[k].lat->N, p.inst[k].chunk, p.n_rec));
+        g.off_mom = off;
+        r_mom = std::max(r_mom, need);
+        if (!compact) off = align_up(off + need);
+    }
+    if (compact) off = align_up(off + r_mom);
     // launches and their table entries
     int64_t entry = 0;
     for (int j = 0; j < p.n_pass; ++j)
@@ -407,6 +418,10 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             g.max_items = std::max(g.max_items, L.n_items);
             L.grid = resident_grid(g.config, g.lds, std::max<int64_t>(L.n_items, 1), g.threads,
                                    g.units);
+            if (n_inst > 1 && waits_for_none(g.config))
+                L.share = (double)L.grid * g.units /
+                          (double)std::max<int64_t>(
+                              1, resident_concurrency(g.config, g.lds, g.threads, g.units));
             p.launches.push_back(L);
         }
     p.n_table = entry;
@@ -539,10 +554,42 @@ ftwa_status launch_by_record(const Plan& p, const ftwa_instance& in, int k, cons
     return FTWA_OK;
 }
 
+// Side branches of a captured run: streams that leave the main one after its
+// spin-split and split groups and join it at the end of the pass.
+constexpr int kSideStreams = 3;
+struct Fork {
+    hipStream_t side[kSideStreams] = {};
+    hipEvent_t out = nullptr, in[kSideStreams] = {};
+    bool create() {
+        bool ok = hipEventCreateWithFlags(&out, hipEventDisableTiming) == hipSuccess;
+        for (int i = 0; i < kSideStreams; ++i)
+            ok = ok && hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking) == hipSuccess &&
+                 hipEventCreateWithFlags(&in[i], hipEventDisableTiming) == hipSuccess;
+        return ok;
+    }
+    ~Fork() {
+        if (out) (void)hipEventDestroy(out);
+        for (int i = 0; i < kSideStreams; ++i) {
+            if (in[i]) (void)hipEventDestroy(in[i]);
+            if (side[i]) (void)hipStreamDestroy(side[i]);
+        }
+    }
+};
+
 // Queues every launch of the run on `stream` (and nothing else: no host
-// synchronisation), so that it can be captured into a graph.
+// synchronisation), so that it can be captured into a graph.  fork (with a
+// capture only): the groups whose workgroups wait for no other run side by
+// side once the spin-split and split groups are through (those fill the chip
+// and need their workgroups resident together), if the chip holds all their
+// workgroups at once, or nearly; otherwise persistent workgroups of several
+// kernels share CUs for the whole run.  Graphs of six lattices of 10 to 96 sites, 64
+// trajectories each, 100 steps: FP32 2.81 ms one after another, 1.57 so; FP64
+// 5.08 and 3.20.  40, 54 and 66 sites FP64, 96 trajectories each, which take
+// somewhat more than the chip, 2.01 and 1.43.  24, 54 and 96 sites FP64, 256
+// each, twice the chip: 3.8 and 5.6; FP32 with 4096 each: 6.0 and 9.2.
+constexpr double kForkShare = 1.25;
 ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStream_t stream,
-                    KernelTimer& timer, bool cooperative) {
+                    KernelTimer& timer, bool cooperative, Fork* fork = nullptr) {
     ftwa_status st;
     uint32_t* status = reinterpret_cast<uint32_t*>(ws + p.off_status);
     Prologue pro;
@@ -664,62 +711,91 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
             return st;
     }
     const ResidentInst* table = reinterpret_cast<const ResidentInst*>(ws + p.r_table);
-    for (int j = 0; j < p.n_pass; ++j) {
-        for (size_t gi = 0; gi < p.groups.size(); ++gi) {
-            const LaunchDesc& Ld = p.launches[(size_t)j * p.groups.size() + gi];
-            if (Ld.n_items == 0) continue;
-            const GroupPlan& g = p.groups[gi];
-            ResidentLaunch L;
-            L.config = g.config;
-            L.lds = g.lds;
-            L.table = table + Ld.first_entry;
-            L.n_entries = Ld.n_entries;
-            L.n_items = Ld.n_items;
-            L.grid = Ld.grid;
-            L.threads = g.threads;
-            L.units = g.units;
-            L.workers = g.workers;
-            L.Nmax = g.Nmax;
-            L.dt = p.dt;
-            L.n_steps = p.n_steps;
-            L.record_every = p.record_every;
-            L.mailbox = ws + g.off_mb;
-            L.error = reinterpret_cast<int*>(status + 1);
-            L.spin_limit = p.spin_limit;
-            L.drop_partners = p.drop_partners;
-            L.cooperative = cooperative;
-            L.unit_hop = Ld.unit_hop;
-            L.dumps = p.dump != nullptr;
-            L.potential = Ld.potential;
-            L.hopping = Ld.hopping;
-            L.interaction = Ld.interaction;
-            if (g.by_record) {
-                if ((st = launch_by_record(p, inst[g.members[0]], g.members[0], Ld, L, ws, stream,
-                                           timer)) != FTWA_OK)
-                    return st;
-                continue;
-            }
-            if ((st = timer.begin(stream)) != FTWA_OK) return st;
-            if ((st = resident_launch(L, stream)) != FTWA_OK) return st;
-            if ((st = timer.end(stream, 1, Ld.work)) != FTWA_OK) return st;
-        }
-        for (int k = 0; k < p.n_inst; ++k) {
+    auto launch_group = [&](int j, size_t gi, hipStream_t q) -> ftwa_status {
+        const LaunchDesc& Ld = p.launches[(size_t)j * p.groups.size() + gi];
+        if (Ld.n_items == 0) return FTWA_OK;
+        const GroupPlan& g = p.groups[gi];
+        ResidentLaunch L;
+        L.config = g.config;
+        L.lds = g.lds;
+        L.table = table + Ld.first_entry;
+        L.n_entries = Ld.n_entries;
+        L.n_items = Ld.n_items;
+        L.grid = Ld.grid;
+        L.threads = g.threads;
+        L.units = g.units;
+        L.workers = g.workers;
+        L.Nmax = g.Nmax;
+        L.dt = p.dt;
+        L.n_steps = p.n_steps;
+        L.record_every = p.record_every;
+        L.mailbox = ws + g.off_mb;
+        L.error = reinterpret_cast<int*>(status + 1);
+        L.spin_limit = p.spin_limit;
+        L.drop_partners = p.drop_partners;
+        L.cooperative = cooperative;
+        L.unit_hop = Ld.unit_hop;
+        L.dumps = p.dump != nullptr;
+        L.potential = Ld.potential;
+        L.hopping = Ld.hopping;
+        L.interaction = Ld.interaction;
+        if (g.by_record)
+            return launch_by_record(p, inst[g.members[0]], g.members[0], Ld, L, ws, q, timer);
+        if ((st = timer.begin(q)) != FTWA_OK) return st;
+        if ((st = resident_launch(L, q)) != FTWA_OK) return st;
+        return timer.end(q, 1, Ld.work);
+    };
+    auto reduce_group = [&](int j, size_t gi, hipStream_t q) -> ftwa_status {
+        for (int k : p.groups[gi].members) {
             const InstPlan& ip = p.inst[k];
-            if (ip.path != FTWA_PATH_RESIDENT) continue;
             const ftwa_instance& in = inst[k];
             int64_t m0, Mc;
             window(p, in, k, j, &m0, &Mc);
             if (Mc <= 0) continue;
             const int N = in.lat->N;
             double* X = reinterpret_cast<double*>(ws + ip.off_x);
-            if ((st = moments_accumulate(2 * N, Mc, p.n_rec, X, in.S1, in.S2, ws + p.r_mom,
-                                         stream)) != FTWA_OK)
+            if ((st = moments_accumulate(2 * N, Mc, p.n_rec, X, in.S1, in.S2,
+                                         ws + p.groups[gi].off_mom, q)) != FTWA_OK)
                 return st;
             if (in.inv &&
                 (st = invariants_accumulate(N, Mc, p.n_rec, in.lat->t, in.U, X,
                                             reinterpret_cast<double*>(ws + ip.off_inv), in.inv,
-                                            stream)) != FTWA_OK)
+                                            q)) != FTWA_OK)
                 return st;
+        }
+        return FTWA_OK;
+    };
+    for (int j = 0; j < p.n_pass; ++j) {
+        std::vector<size_t> apart;  // the groups that run side by side
+        if (fork && p.groups.size() > 1) {
+            double share = 0;
+            for (size_t gi = 0; gi < p.groups.size(); ++gi) {
+                const LaunchDesc& Ld = p.launches[(size_t)j * p.groups.size() + gi];
+                if (!waits_for_none(p.groups[gi].config) || Ld.n_items == 0) continue;
+                apart.push_back(gi);
+                share += Ld.share;
+            }
+            if (share > kForkShare) apart.clear();
+        }
+        for (size_t gi = 0; gi < p.groups.size(); ++gi)
+            if (std::find(apart.begin(), apart.end(), gi) == apart.end() &&
+                (st = launch_group(j, gi, stream)) != FTWA_OK)
+                return st;
+        if (!apart.empty()) FTWA_HIP_TRY(hipEventRecord(fork->out, stream));
+        for (size_t n = 0; n < apart.size(); ++n) {
+            hipStream_t q = fork->side[n % kSideStreams];
+            if (n < kSideStreams) FTWA_HIP_TRY(hipStreamWaitEvent(q, fork->out, 0));
+            if ((st = launch_group(j, apart[n], q)) != FTWA_OK ||
+                (st = reduce_group(j, apart[n], q)) != FTWA_OK)
+                return st;
+        }
+        for (size_t gi = 0; gi < p.groups.size(); ++gi)
+            if (std::find(apart.begin(), apart.end(), gi) == apart.end() &&
+                (st = reduce_group(j, gi, stream)) != FTWA_OK)
+                return st;
+        for (size_t n = 0; n < apart.size() && n < kSideStreams; ++n) {
+            FTWA_HIP_TRY(hipEventRecord(fork->in[n], fork->side[n]));
+            FTWA_HIP_TRY(hipStreamWaitEvent(stream, fork->in[n], 0));
         }
     }
     // ---- non-finite trajectories counted by the invariant monitors
@@ -976,9 +1052,10 @@ ftwa_status ftwa_evolve_static(const ftwa_instance* inst, int n_inst, double dt,
     Plan plan;
     if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan)) != FTWA_OK)
         return st;
-    // the split kernel's mailboxes are larger than a few trajectories' stream chunks
+    // the split kernel's mailboxes are larger than a few trajectories' stream
+    // chunks, and groups that may run side by side have scratch of their own
     if (plan.total > kStaticScratchBytes &&
-        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, false)) !=
+        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, true)) !=
             FTWA_OK)
         return st;
     if (plan.total > kStaticScratchBytes)
@@ -1024,10 +1101,16 @@ ftwa_status ftwa_evolve_graph(const ftwa_instance* inst, int n_inst, double dt, 
         delete g;
         return fail(FTWA_EHIP, "hipStreamCreateWithFlags");
     }
+    Fork fork;
+    if (!fork.create()) {
+        (void)hipStreamDestroy(cs);
+        delete g;
+        return fail(FTWA_EHIP, "streams of a graph's branches");
+    }
     KernelTimer off(false);
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        st = execute(g->plan, g->inst.data(), g->ws, cs, off, false);
+        st = execute(g->plan, g->inst.data(), g->ws, cs, off, false, &fork);
         hipError_t e2 = hipStreamEndCapture(cs, &g->graph);
         if (st == FTWA_OK && e2 != hipSuccess) st = hip_fail(e2, "hipStreamEndCapture");
     } else {

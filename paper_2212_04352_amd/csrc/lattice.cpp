@@ -1168,7 +1168,8 @@ ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>
     }
     // One deal per class and lane count: the diagonal at the density that the
     // shortest first pass needs.  They take 0.2 to 0.9 ms each at 54 sites, so
-    // they run side by side.
+    // they run side by side; below 32 sites a thread costs more than the deal.
+    const std::launch how = N < 32 ? std::launch::deferred : std::launch::async;
     std::map<int, size_t> per;
     for (const auto& [I, n_pass, n_list] : shapes) {
         const size_t groups = (size_t)n_pass / (I >= 16 ? 1 : (size_t)(16 / I));
@@ -1177,7 +1178,7 @@ ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>
     std::map<int, std::future<std::vector<uint32_t>>> dealing[2];
     for (const auto& [I, density] : per)
         for (int odd = 0; odd < 2; ++odd)
-            dealing[odd][I] = std::async(std::launch::async, [lat, N, odd, I = I, density = density] {
+            dealing[odd][I] = std::async(how, [lat, N, odd, I = I, density = density] {
                 return shared_deal(shared_entries(*lat, odd != 0, I), odd ? 0 : (size_t)N, I,
                                    density);
             });
