@@ -1,6 +1,7 @@
 // evolve_resident.hip -- host side of the resident path: which kernel
 // configuration holds a lattice, its LDS and scratch, its grid and launch.
 #include <algorithm>
+#include <set>
 
 #include "device_common.h"
 #include "ftwa_internal.h"
@@ -13,10 +14,11 @@ namespace {
 
 // The public configuration index.  0-7 and 13-18: the first tiles with every
 // slot general and with one general slot per class; 8-12: the spin split;
-// 19-22: the split kernel; 23-24: FP64 tiles of 384 threads x 2 units with
+// 19-22 and 37: the split kernel; 23-24: FP64 tiles of 384 threads x 2 units with
 // (2, 2) slots (the 768 entries per class of 256 x (3, 3) with two thirds of
 // its registers per thread); 25-36: fewer units per workgroup (the per-stage
-// barriers span fewer waves and more workgroups share a CU).
+// barriers span fewer waves and more workgroups share a CU).  From 38 on: the
+// shared-pack shapes, FP64 then FP32.
 const Config* const kConfigTable[] = {
     &kConfigsF64Shared[0], &kConfigsF64Shared[1], &kConfigsF64Shared[2],
     &kConfigsF64Shared[3], &kConfigsF32Shared[0], &kConfigsF32Shared[1],
@@ -76,14 +78,35 @@ int64_t split_words(const Config& c) {
 }  // namespace
 
 namespace {
+
+// Facts of a device that every plan asks for: its compute units, the
+// configurations whose LDS limit is raised, and the workgroups of a
+// configuration that a CU holds.  Asking the runtime again took 2.3 of the
+// 6.5 us of a plan (a run plans twice: for its workspace and for itself) and as
+// much again before the launches.
+struct DeviceFacts {
+    int cus = 0;
+    std::set<int> prepared;
+    std::map<std::tuple<int, int, size_t>, int> per_cu;  // configuration, threads, LDS
+};
+constexpr size_t kMaxFacts = 4096;  // distinct launch shapes kept per device
+std::mutex g_facts_mu;
+std::map<int, DeviceFacts> g_facts;
+
 int device_cus() {
     int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
+    if (hipGetDevice(&dev) != hipSuccess) return cus;
+    std::lock_guard<std::mutex> lock(g_facts_mu);
+    DeviceFacts& f = g_facts[dev];
+    if (f.cus == 0 &&
+        (hipDeviceGetAttribute(&f.cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+         f.cus < 1)) {
+        f.cus = 0;
+        return cus;
     }
-    return cus;
+    return f.cus;
 }
+
 }  // namespace
 
 namespace {
@@ -378,8 +401,8 @@ bool resident_has_interaction(int config) {
 }
 
 
-ftwa_status resident_prepare(int config, size_t lds) {
-    (void)lds;  // the limit is raised to the whole LDS once; launches use less
+namespace {
+ftwa_status raise_lds_limit(int config) {
     if (const SharedShape* sh = shared_at(config)) {
         for (int v = 0; v < 4; ++v)
             for (const void* f : {sh->fn[v], sh->fn_t1[v]})
@@ -402,6 +425,19 @@ ftwa_status resident_prepare(int config, size_t lds) {
             FTWA_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                              (int)kMaxLds));
     return FTWA_OK;
+}
+}  // namespace
+
+ftwa_status resident_prepare(int config, size_t lds) {
+    (void)lds;  // the limit is raised to the whole LDS once; launches use less
+    int dev = 0;
+    FTWA_HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lock(g_facts_mu);
+    DeviceFacts& f = g_facts[dev];
+    if (f.prepared.count(config)) return FTWA_OK;
+    const ftwa_status st = raise_lds_limit(config);
+    if (st == FTWA_OK) f.prepared.insert(config);
+    return st;
 }
 
 // Pairs of spin-split workgroups that are resident together: one workgroup
@@ -428,11 +464,20 @@ int64_t resident_concurrency(int config, size_t lds, int threads, int units) {
     const void* fn = sh ? sh->fn[kSharedPlain] : config_at(config).fn;
     // the occupancy query honours the dynamic-LDS limit of the kernel
     if (resident_prepare(config, kMaxLds) != FTWA_OK) return (int64_t)device_cus() * units;
-    int per_cu = 1;
+    const int64_t cus = device_cus();
+    int dev = 0, per_cu = 1;
+    if (hipGetDevice(&dev) != hipSuccess) return cus * units;
+    std::lock_guard<std::mutex> lock(g_facts_mu);
+    auto& known = g_facts[dev].per_cu;
+    const auto key = std::make_tuple(config, threads, lds);
+    auto it = known.find(key);
+    if (it != known.end()) return it->second * cus * units;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess ||
         per_cu < 1)
-        per_cu = 1;
-    return (int64_t)per_cu * device_cus() * units;
+        return cus * units;
+    if (known.size() >= kMaxFacts) known.clear();
+    known.emplace(key, per_cu);
+    return (int64_t)per_cu * cus * units;
 }
 
 int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int units) {
