@@ -284,7 +284,10 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     const int spin0 = member / G, part = member % G;
     const int group = (k / (2 * G)) * 8 + xcd;
     const int64_t n_groups = gridDim.x / (2 * G);
-    if (tid0 == 0) *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8)) = 0;
+    // (a launch of the same run that gave up before this one leaves its mark)
+    if (tid0 == 0)
+        *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8)) =
+            __hip_atomic_load(A.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // published words of this group: [2 spins][G parts][2 parities][W][kPlane],
     // the stage every wave of every member has published its even and its
     // odd elements of, then every member's XCD; a byte offset holds a member's
@@ -369,6 +372,7 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
             return v;
         };
         __syncthreads();  // the previous item is done with LDS
+        if (abort_flag) return;
 
         // ---- the trajectory's own elements, the halo, the zero and scratch
         // slots, and the partner's diagonal
