@@ -6,7 +6,7 @@
 namespace ftwa {
 
 // Pause between two looks at stale flags, in units of 64 cycles.
-constexpr int kSplitSleep = 4;
+constexpr int kSplitSleep = 1;
 
 // ---------------------------------------------------------------- split kernel
 // A spin block too large for one CU (the 198-site block in FP64: 315 KB)
@@ -20,9 +20,9 @@ constexpr int kSplitSleep = 4;
 // copies in its halo and the partner spin's diagonal.
 //
 // Every wave of every part has a flag per class: the last stage whose even
-// (odd) exports it has published.  It raises the flag a slot or more after
-// its last export, when the stores have reached the L2 anyway, and no barrier
-// is spent on it.  A reader looks at the flags of all members (one load, a
+// (odd) exports it has published.  It raises the even flag a slot after its
+// last export, when the stores have reached the L2 anyway, the odd flag at
+// once, and no barrier is spent on it.  A reader looks at the flags of all members (one load, a
 // flag per lane) a slot before it needs them, then reads the values, two
 // 8-byte words each in FP64, while it computes the following slots.  The XCD's
 // L2 is what the members share: they compare their XCDs once per launch, and
@@ -41,13 +41,13 @@ constexpr int kSplitSleep = 4;
 // the most time to arrive: the even elements of a part are ordered interior
 // (they read no other part's element) before boundary (the diagonal and the
 // exported ones), exported odd elements come first in theirs.  The odd halo
-// is read during the last interior slots and landed before the boundary ones;
+// is read during the last interior slot and landed before the boundary ones;
 // the even halo of the next stage and the partner's diagonal are read during
 // the last odd slots and landed at the end of the stage.
 //
 // What bounds it: a stage's chain of element slots and exchanges, not the
-// ALUs (VALU busy about 40 %).  198 sites, 512 trajectories, 50 steps: 14.4 ms,
-// 1.78e6 trajectory-steps/s, 5.4 us a stage and group; 27.5 ms before, when
+// ALUs (VALU busy about 40 %).  198 sites, 512 trajectories, 50 steps: 14.2 ms,
+// 1.8e6 trajectory-steps/s, 5.4 us a stage and group; 27.5 ms before, when
 // every 32-bit word carried its stage number and was written through to
 // memory (twice the bytes, four loads and stores an element, and a wait for
 // the stores' round trip at every descriptor behind them).  150 sites, 500
@@ -268,13 +268,17 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
                                                    // after kEnt takes what nobody reads)
     constexpr int kEvenPad = NTU * UE;
     constexpr uint32_t kDiagCopy = 256 * TB;
-    static_assert(GE1 <= UB && UB < UE && UB + GE2 <= UE && GO <= UO && XO <= UO,
+    static_assert(UB >= 2 && GE1 <= UB && UB < UE && UB + GE2 <= UE && GO <= UO && XO <= UO,
                   "slot groups within their class");
     static_assert((POT ? 1 : 0) + (GINT ? 1 : 0) + (HOP ? 1 : 0) <= 1,
                   "one of a potential, a general interaction and complex hopping");
     extern __shared__ __align__(16) unsigned char smem[];
     (void)smem;
     const int tid0 = threadIdx.x;
+    // an earlier launch of this run gave up: nothing to wait for
+    if (__builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(A.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+        return;
 
     // groups of 2G workgroups on one XCD (blocks b = xcd + 8 k; members k =
     // 2G c .. 2G c + 2G - 1): spin = member / G, part = member % G; the
@@ -284,10 +288,7 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     const int spin0 = member / G, part = member % G;
     const int group = (k / (2 * G)) * 8 + xcd;
     const int64_t n_groups = gridDim.x / (2 * G);
-    // (a launch of the same run that gave up before this one leaves its mark)
-    if (tid0 == 0)
-        *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8)) =
-            __hip_atomic_load(A.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid0 == 0) *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8)) = 0;
     // published words of this group: [2 spins][G parts][2 parities][W][kPlane],
     // the stage every wave of every member has published its even and its
     // odd elements of, then every member's XCD; a byte offset holds a member's
@@ -372,7 +373,6 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
             return v;
         };
         __syncthreads();  // the previous item is done with LDS
-        if (abort_flag) return;
 
         // ---- the trajectory's own elements, the halo, the zero and scratch
         // slots, and the partner's diagonal
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
             // ---------------- phase 1: even elements (next values held)
 #pragma unroll
             for (int u = 0; u < UE; ++u) {
-                constexpr int UL = UB > 2 ? UB - 2 : 1;
+                constexpr int UL = UB - 1;
                 if (u == UL - 1) fl = look(1);
                 if (u == UL && u < UB) {
                     // (also in an item's first stage: no member overwrites
@@ -674,12 +674,16 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
             // the partner's diagonal of the next stage's input is read
             // meanwhile (into the copy this stage does not read)
             uint64_t dw = 0;
+            // slots before the end at which the even flags are awaited: with few
+            // slots the members' flags need the time (110 sites, (4, 4): one 6.6 ms,
+            // two 7.5; 150 sites, (6, 6): 7.35 and 7.30)
+            constexpr int AE = UO > 4 ? 2 : 1;
 #pragma unroll
             for (int u = UE; u < UE + UO; ++u) {
                 if (u == UE + 1) signal(0, stamp);
-                if (u == UE + XO + 1) signal(1, stamp);
-                if (u == UE + UO - 3) fl = look(0);
-                if (u == UE + UO - 2) {
+                if (u == UE + XO) signal(1, stamp);
+                if (u == UE + UO - AE - 1) fl = look(0);
+                if (u == UE + UO - AE) {
                     // every member is past its phase 1: the partner's diagonal
                     // and the even halo of the next stage's input
                     await(0, fl, stamp);
@@ -709,7 +713,7 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
                 if (xp) export_elem(d, nx);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if constexpr (XO + 1 >= UO) signal(1, stamp);
+            if constexpr (XO >= UO) signal(1, stamp);
             if (t < N) {
                 T x;
                 real_of(dw, x);
