@@ -6,7 +6,9 @@
 #include <deque>
 #include <future>
 #include <map>
+#include <new>
 #include <set>
+#include <system_error>
 #include <unordered_map>
 #include <utility>
 
@@ -1175,16 +1177,26 @@ ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>
         const size_t groups = (size_t)n_pass / (I >= 16 ? 1 : (size_t)(16 / I));
         per[I] = std::max(per[I], ((size_t)N + groups - 1) / groups);
     }
-    std::map<int, std::future<std::vector<uint32_t>>> dealing[2];
-    for (const auto& [I, density] : per)
-        for (int odd = 0; odd < 2; ++odd)
-            dealing[odd][I] = std::async(how, [lat, N, odd, I = I, density = density] {
-                return shared_deal(shared_entries(*lat, odd != 0, I), odd ? 0 : (size_t)N, I,
-                                   density);
-            });
     std::map<int, std::vector<uint32_t>> dealt[2];
-    for (int odd = 0; odd < 2; ++odd)
-        for (auto& [I, f] : dealing[odd]) dealt[odd][I] = f.get();
+    try {
+        std::map<int, std::future<std::vector<uint32_t>>> dealing[2];
+        for (const auto& [I, density] : per)
+            for (int odd = 0; odd < 2; ++odd) {
+                auto deal = [lat, N, odd, I = I, density = density] {
+                    return shared_deal(shared_entries(*lat, odd != 0, I), odd ? 0 : (size_t)N, I,
+                                       density);
+                };
+                try {
+                    dealing[odd][I] = std::async(how, deal);
+                } catch (const std::system_error&) {  // no thread to be had
+                    dealing[odd][I] = std::async(std::launch::deferred, deal);
+                }
+            }
+        for (int odd = 0; odd < 2; ++odd)
+            for (auto& [I, f] : dealing[odd]) dealt[odd][I] = f.get();
+    } catch (const std::bad_alloc&) {
+        return fail(FTWA_ENOMEM, "dealing the shared-pack lists");
+    }
     std::map<std::array<int, 3>, size_t> at;
     std::vector<uint32_t> t;
     for (const auto& shape : shapes) {
