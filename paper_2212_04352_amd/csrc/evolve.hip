@@ -576,13 +576,44 @@ struct Fork {
     }
 };
 
+// Whether instances of different groups write to the same memory (slices of an
+// ensemble whose moments meet in one S1 and S2, say): such groups keep their
+// order on one stream.
+bool groups_share_outputs(const Plan& p, const ftwa_instance* inst) {
+    struct Range {
+        const char *lo, *hi;
+        int group;
+    };
+    std::vector<Range> all;
+    for (int k = 0; k < p.n_inst; ++k) {
+        const ftwa_instance& in = inst[k];
+        const int N = in.lat->N;
+        auto add = [&](const void* at, size_t bytes) {
+            const char* lo = static_cast<const char*>(at);
+            if (lo && bytes > 0) all.push_back({lo, lo + bytes, p.inst[k].group});
+        };
+        add(in.rho, (size_t)2 * packed_count(N) * in.n_traj * cplx_bytes(p.dtype));
+        add(in.S1, (size_t)p.n_rec * 2 * N * sizeof(double));
+        add(in.S2, (size_t)p.n_rec * s2_count(2 * N) * sizeof(double));
+        add(in.inv, (size_t)p.n_rec * 4 * sizeof(double));
+    }
+    std::sort(all.begin(), all.end(), [](const Range& a, const Range& b) { return a.lo < b.lo; });
+    Range far = {nullptr, nullptr, -1};  // the range so far that ends last
+    for (const Range& r : all) {
+        if (r.lo < far.hi && r.group != far.group) return true;
+        if (r.hi > far.hi) far = r;
+    }
+    return false;
+}
+
 // Queues every launch of the run on `stream` (and nothing else: no host
 // synchronisation), so that it can be captured into a graph.  fork (with a
 // capture only): the groups whose workgroups wait for no other run side by
 // side once the spin-split and split groups are through (those fill the chip
 // and need their workgroups resident together), if the chip holds all their
 // workgroups at once, or nearly; otherwise persistent workgroups of several
-// kernels share CUs for the whole run.  Graphs of six lattices of 10 to 96 sites, 64
+// kernels share CUs for the whole run.  Groups that write to the same memory stay
+// in order.  Graphs of six lattices of 10 to 96 sites, 64
 // trajectories each, 100 steps: FP32 2.81 ms one after another, 1.57 so; FP64
 // 5.08 and 3.20.  40, 54 and 66 sites FP64, 96 trajectories each, which take
 // somewhat more than the chip, 2.01 and 1.43.  24, 54 and 96 sites FP64, 256
@@ -765,9 +796,10 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
         }
         return FTWA_OK;
     };
+    const bool may_fork = fork && p.groups.size() > 1 && !groups_share_outputs(p, inst);
     for (int j = 0; j < p.n_pass; ++j) {
         std::vector<size_t> apart;  // the groups that run side by side
-        if (fork && p.groups.size() > 1) {
+        if (may_fork) {
             double share = 0;
             for (size_t gi = 0; gi < p.groups.size(); ++gi) {
                 const LaunchDesc& Ld = p.launches[(size_t)j * p.groups.size() + gi];

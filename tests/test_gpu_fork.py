@@ -49,3 +49,40 @@ def test_side_by_side_groups(ft, dtype, extra, M, chunk):
             assert torch.equal(p.rho, q.rho)
             assert torch.allclose(p.S1, q.S1, rtol=1e-12, atol=1e-12)
             assert torch.allclose(p.S2, q.S2, rtol=1e-12, atol=1e-12)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_groups_with_shared_moments_keep_their_order(ft, dtype):
+    """Two instances of different groups (one with a potential) whose moments
+    meet in one S1 and S2: every replay gives the sum of both runs."""
+    import torch
+    lat, M, steps, every = ft.Lattice("torus", 2, 3), 40, 8, 4
+    potential = {"v_site": torch.linspace(-1, 1, lat.N, dtype=torch.float64, device="cuda"),
+                 "v_env": torch.ones(2 * steps + 1, dtype=torch.float64, device="cuda")}
+
+    def problems():
+        out = [ft.Problem.allocate(lat, 2.0, M, lat.fock_start("neel"), dtype, traj_offset=k * M)
+               for k in range(2)]
+        for name, value in potential.items():
+            setattr(out[1], name, value)
+        ft.sample(out, 5)
+        return out
+
+    single, pair = problems(), problems()
+    for q in single:
+        ft.evolve(q, 0.02, steps, every)
+    S1, S2 = (sum(getattr(q, name) for q in single) for name in ("S1", "S2"))
+    starts = [p.rho.clone() for p in pair]
+    pair[0].ensure_moments(steps // every + 1)
+    pair[1].S1, pair[1].S2 = pair[0].S1, pair[0].S2
+    graph = ft.EvolveGraph(pair, 0.02, steps, every)
+    for _ in range(5):
+        for p, s in zip(pair, starts):
+            p.rho.copy_(s)
+        torch.cuda.synchronize()
+        graph.launch()
+        graph.check()
+        for p, q in zip(pair, single):
+            assert torch.equal(p.rho, q.rho)
+        assert torch.allclose(pair[0].S1, S1, rtol=1e-12, atol=1e-12)
+        assert torch.allclose(pair[0].S2, S2, rtol=1e-12, atol=1e-12)
