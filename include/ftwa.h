@@ -309,12 +309,14 @@ typedef struct {
        up and the run reports FTWA_ETIMEOUT (0 = the default, about 2 s of
        polling). */
     unsigned spin_limit;
-    /* Fault injection for tests of the timeout path; 0 in every production
-       call.  Nonzero: every launch of a spin-split configuration (one
-       workgroup per spin block) runs only the up-spin workgroups of eight
-       pairs, whose partners are absent, so each of them gives up its first
-       wait after spin_limit polls and exits; rho is left as it was and
-       ftwa_evolve_check reports FTWA_ETIMEOUT. */
+    /* Fault injection for tests; 0 in every production call.
+       2: the FP64 split kernel's workgroups exchange their boundaries as they
+       do where they run on different XCDs (same results, slower).
+       Any other nonzero value: every launch of a configuration whose
+       trajectories span several workgroups runs only the up-spin workgroups
+       of eight trajectories, whose partners are absent, so each of them gives
+       up its first wait for them after spin_limit polls and exits; rho is left
+       as it was and ftwa_evolve_check reports FTWA_ETIMEOUT. */
     int drop_partners;
 } ftwa_tuning;
 

@@ -217,7 +217,7 @@ def _instances(insts):
 def _tuning(path: str = "auto", traj_chunk: int = 0, timing=None, config: int = -1,
             spin_limit: int = 0, drop_partners: bool = False):
     t = Tuning(PATH[path], int(traj_chunk), int(config), None, None, None, int(spin_limit),
-               1 if drop_partners else 0)
+               int(drop_partners))
     if timing is not None:
         t.kernel_ms = ctypes.pointer(timing["ms"])
         t.kernel_launches = ctypes.pointer(timing["launches"])

@@ -164,7 +164,7 @@ struct Plan {
     // written to r_table by kernels queued at the start of every run
     std::vector<ResidentInst> table;
     unsigned spin_limit = 0;   // 0: the kernels' default
-    bool drop_partners = false;
+    int inject = 0;            // ftwa_tuning's drop_partners
 };
 
 void window(const Plan& p, const ftwa_instance& in, int k, int j, int64_t* m0, int64_t* Mc) {
@@ -199,7 +199,9 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
     if (force >= resident_config_count()) return fail(FTWA_EINVAL, "resident_config out of range");
     const int64_t user_chunk = tune && tune->traj_chunk > 0 ? tune->traj_chunk : 0;
     p.spin_limit = tune ? tune->spin_limit : 0;
-    p.drop_partners = tune && tune->drop_partners;
+    p.inject = !tune || !tune->drop_partners ? 0
+               : tune->drop_partners == kInjectFarExchange ? kInjectFarExchange
+                                                           : kInjectDropPartners;
 
     // ---- path and configuration of every instance
     // (8 config + 4 (general interaction) + 2 (complex hopping) + (external
@@ -763,7 +765,7 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
         L.mailbox = ws + g.off_mb;
         L.error = reinterpret_cast<int*>(status + 1);
         L.spin_limit = p.spin_limit;
-        L.drop_partners = p.drop_partners;
+        L.inject = p.inject;
         L.cooperative = cooperative;
         L.unit_hop = Ld.unit_hop;
         L.dumps = p.dump != nullptr;

@@ -606,11 +606,12 @@ ftwa_status resident_launch(const ResidentLaunch& L, hipStream_t stream) {
     A.tail_off = (uint32_t)(L.lds - lds_tail(c));
     A.error = L.error;
     A.spin_limit = L.spin_limit ? L.spin_limit : (c.G > 1 ? kSplitSpinLimit : kSpinLimit);
+    A.far = L.inject == kInjectFarExchange;
     void* args[] = {&A};
     // fault injection for tests of the timeout path: only the up-spin
-    // workgroups of eight pairs run, so that each of them gives up its first
-    // wait for the absent partner and exits
-    const int64_t grid = (L.drop_partners && c.S == 1 && c.G == 1) ? 8 : L.grid;
+    // workgroups of eight trajectories run, so that each of them gives up its
+    // first wait for the absent partners and exits
+    const int64_t grid = L.inject == kInjectDropPartners && c.S == 1 ? 8 * c.G : L.grid;
     const bool t1 = L.unit_hop && !L.dumps;
     const void* fn = L.interaction ? (t1 && c.fn_gint_t1 ? c.fn_gint_t1 : c.fn_gint)
                      : L.hopping   ? (t1 && c.fn_hop_t1 ? c.fn_hop_t1 : c.fn_hop)
@@ -624,7 +625,7 @@ ftwa_status resident_launch(const ResidentLaunch& L, hipStream_t stream) {
         // every word starts at stage 0, which no wait accepts (a fill kernel,
         // no memset node)
         ftwa_status st = zero_words(static_cast<unsigned*>(L.mailbox),
-                                    (int64_t)mailbox_words(c, L.Nmax, grid) * 2, stream);
+                                    (int64_t)mailbox_words(c, L.Nmax, L.grid) * 2, stream);
         if (st != FTWA_OK) return st;
         // both workgroups of a pair must be resident at the same time: the
         // grid never exceeds one workgroup per CU; a cooperative launch checks

@@ -348,6 +348,9 @@ struct ResidentInst {
     int n_a;               // shared-pack kernel: sites of the first sublattice
     const uint32_t* stab;  // shared-pack kernel: the dealt lists (shared_lists)
 };
+// Values of ftwa_tuning's drop_partners (any other one that is not zero means
+// the first).
+constexpr int kInjectDropPartners = 1, kInjectFarExchange = 2;
 struct ResidentLaunch {
     int config;
     size_t lds;                 // dynamic LDS: max over the entries
@@ -363,7 +366,7 @@ struct ResidentLaunch {
     void* mailbox;              // resident_mailbox_bytes(config, Nmax, n_items) of scratch
     int* error;                 // the run's timeout word (set to 1 by a wait that gave up)
     unsigned spin_limit;        // polls before a bounded wait gives up (0: the default)
-    bool drop_partners;         // fault injection: run only one workgroup of each pair
+    int inject;                 // ftwa_tuning's drop_partners: kInject*
     bool cooperative;           // false under graph capture
     bool unit_hop;              // every instance of the launch has t = 1
     bool dumps;                 // an entry stores its state at records (ResidentInst::dump)

@@ -19,6 +19,7 @@ struct ResidentArgs {
     uint32_t tail_off;          // LDS byte offset of the record sums and the abort flag
     int* error;                 // set to 1 when a wait times out
     unsigned spin_limit;        // polls before a bounded wait gives up
+    int far;                    // split kernel, nonzero: exchange as across XCDs
 };
 
 constexpr unsigned kSpinLimit = 1u << 26;  // default: ~2 s of polling

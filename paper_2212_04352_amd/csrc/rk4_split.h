@@ -27,8 +27,11 @@ constexpr int kSplitSleep = 1;
 // 8-byte words each in FP64, while it computes the following slots.  The XCD's
 // L2 is what the members share: they compare their XCDs once per launch, and
 // where all are one, published words stop at the L2 (`near`) instead of being
-// written through to memory.  Otherwise the stores, the fences and the loads
-// are those of the agent scope.
+// written through to memory.  That rests on this chip, not on the memory model
+// (which asks for agent scope between workgroups): one L2 per XCD, first-level
+// caches that write through to it, and a store counted off by vmcnt once the L2
+// has it.  Otherwise the stores, the fences and the loads are those of the agent
+// scope.
 //
 // No word is overwritten before it is read: a part publishes into an area
 // again two stages later, after it has waited there for the odd flags of all
@@ -275,10 +278,16 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     (void)smem;
     const int tid0 = threadIdx.x;
-    // an earlier launch of this run gave up: nothing to wait for
-    if (__builtin_amdgcn_readfirstlane(
-            __hip_atomic_load(A.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-        return;
+    // An earlier launch of this run gave up: nothing to wait for.  One thread
+    // looks and the workgroup leaves as one, also where another group gives up
+    // meanwhile.
+    {
+        int& gave_up = *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8));
+        if (tid0 == 0)
+            gave_up = __hip_atomic_load(A.error, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(gave_up)) return;
+    }
 
     // groups of 2G workgroups on one XCD (blocks b = xcd + 8 k; members k =
     // 2G c .. 2G c + 2G - 1): spin = member / G, part = member % G; the
@@ -288,7 +297,6 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     const int spin0 = member / G, part = member % G;
     const int group = (k / (2 * G)) * 8 + xcd;
     const int64_t n_groups = gridDim.x / (2 * G);
-    if (tid0 == 0) *reinterpret_cast<int*>(lds_ptr(A.tail_off + (NTU / 64) * 2 * 8)) = 0;
     // published words of this group: [2 spins][G parts][2 parities][W][kPlane],
     // the stage every wave of every member has published its even and its
     // odd elements of, then every member's XCD; a byte offset holds a member's
@@ -300,7 +308,8 @@ __global__ __launch_bounds__(NTU) void rk4_split(ResidentArgs A) {
     auto xword = [&](int spin, uint32_t qs) {
         return ((uint32_t)((spin * G + (int)(qs >> 16)) * 2 * kPlane * W) + (qs & 0xffffu)) * 8u;
     };
-    const bool near = same_xcd<G>(xg + (size_t)2 * G * 2 * kPlane * W + 64, member, A.spin_limit);
+    const bool near =
+        !A.far && same_xcd<G>(xg + (size_t)2 * G * 2 * kPlane * W + 64, member, A.spin_limit);
     int64_t g = 0;  // stage counter (continues across items)
 
     C y[UE + UO], acc[UE + UO], hold[UE];
