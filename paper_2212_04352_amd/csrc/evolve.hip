@@ -438,6 +438,18 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
     return FTWA_OK;
 }
 
+// The table of a resident plan (not of the shared packs').
+TableShape table_shape(const ResidentPlan& rp, ftwa_dtype dtype) {
+    TableShape sh;
+    sh.G = resident_parts(rp.config);
+    sh.even_slots = rp.even_slots;
+    sh.odd_slots = rp.odd_slots;
+    if (sh.G > 1) sh.bnd_entry = rp.bnd_entry;
+    else sh.compact = resident_spins(rp.config) == 1;
+    sh.elem_bytes = (int)cplx_bytes(dtype);
+    return sh;
+}
+
 // Host work before the launches, nothing queued: the launch-table entries
 // (their descriptor tables looked up; ftwa_lattice_upload created them) and
 // the kernels' LDS limits.  Not under graph capture.
@@ -462,21 +474,14 @@ ftwa_status build_table(Plan& p, const ftwa_instance* inst, char* ws) {
                 e.ldr = inst[k].n_traj;
                 e.part_words = 0;
                 e.hmax = 0;
-                if (resident_parts(g.config) > 1) {
-                    if ((st = split_tables(inst[k].lat, resident_parts(g.config),
-                                           ip.res.even_slots, ip.res.odd_slots, ip.res.bnd_entry,
-                                           (int)cplx_bytes(p.dtype), &e.desc, &e.part_words,
-                                           &e.hmax)) != FTWA_OK)
+                if (resident_is_shared(g.config)) {
+                    if ((st = shared_lists(inst[k].lat, ip.res.lanes, &e.stab)) != FTWA_OK)
                         return st;
-                } else if (resident_is_shared(g.config)) {
-                    if ((st = shared_lists(inst[k].lat, ip.res.lanes, ip.res.workers / ip.res.lanes,
-                                           (int)ip.res.even_slots, &e.stab)) != FTWA_OK)
-                        return st;
-                } else if ((st = padded_descriptors(inst[k].lat, ip.res.even_slots,
-                                                    ip.res.odd_slots, (int)cplx_bytes(p.dtype),
-                                                    resident_spins(g.config) == 1, &e.desc)) !=
-                           FTWA_OK) {
-                    return st;
+                } else {
+                    const TableShape sh = table_shape(ip.res, p.dtype);
+                    st = sh.G > 1 ? split_tables(inst[k].lat, sh, &e.desc, &e.part_words, &e.hmax)
+                                  : padded_descriptors(inst[k].lat, sh, &e.desc);
+                    if (st != FTWA_OK) return st;
                 }
                 DeviceTables tab;
                 if ((st = device_tables(inst[k].lat, &tab)) != FTWA_OK) return st;
@@ -982,53 +987,30 @@ extern "C" {
 
 ftwa_status ftwa_lattice_upload(ftwa_lattice lat) {
     if (!lat) return fail(FTWA_EINVAL, "ftwa_lattice_upload: NULL lattice");
-    ftwa_status st = upload_tables(lat);
-    if (st != FTWA_OK) return st;
-    const DeviceTables& tab = host_tables(lat);
-    if (!tab.bipartite) return FTWA_OK;  // the stream path needs no descriptors
     int dev = 0;
     FTWA_HIP_TRY(hipGetDevice(&dev));
-    const int N = lat->N;
+    if (uploaded(lat, dev)) return FTWA_OK;
+    const DeviceTables& tab = host_tables(lat);
+    ftwa_status st;
+    std::vector<TableShape> shapes;
+    std::set<int> configs;
     // every table a plan may look up: each configuration that holds the
     // lattice, in either precision, with and without the potential's layout
+    // (a lattice that is not bipartite takes the stream path, which needs none)
     for (int c = 0; c < resident_config_count(); ++c)
         for (ftwa_dtype dtype : {FTWA_F64, FTWA_F32})
             for (bool pot : {false, true}) {
                 ResidentPlan rp;
-                if (!resident_plan(N, dtype, tab, &rp, c, true, pot)) continue;
-                if (resident_is_shared(c)) continue;
-                const int eb = (int)cplx_bytes(dtype);
-                const void* d = nullptr;
-                std::string key;
-                if (resident_parts(c) > 1) {
-                    int pw = 0, hm = 0;
-                    st = split_tables(lat, resident_parts(c), rp.even_slots, rp.odd_slots,
-                                      rp.bnd_entry, eb, &d, &pw, &hm, true);
-                    key = split_key(dev, resident_parts(c), rp.even_slots, rp.odd_slots,
-                                    rp.bnd_entry, eb);
-                } else {
-                    st = padded_descriptors(lat, rp.even_slots, rp.odd_slots, eb,
-                                            resident_spins(c) == 1, &d, true);
-                    key = padded_key(dev, rp.even_slots, rp.odd_slots, eb, resident_spins(c) == 1);
-                }
-                if (st == FTWA_EHIP || st == FTWA_ENOMEM) return st;
-                if (st != FTWA_OK) {
-                    // this configuration cannot hold the lattice after all: a
-                    // plan that picks it reports the same error
-                    std::lock_guard<std::mutex> lock(lat->mu);
-                    lat->table_err[key] = std::make_pair(st, std::string(ftwa_last_error()));
-                }
-                if ((st = resident_prepare(c, rp.lds)) != FTWA_OK) return st;
+                if (resident_is_shared(c) ||
+                    !resident_plan(lat->N, dtype, tab, &rp, c, true, pot))
+                    continue;
+                shapes.push_back(table_shape(rp, dtype));
+                configs.insert(c);
             }
-    std::vector<std::array<int, 3>> shapes;
-    std::set<int> ready;
-    for (const ResidentPlan& rp : shared_plans(N, tab)) {
-        shapes.push_back({rp.lanes, rp.workers / rp.lanes, (int)rp.even_slots});
-        if (!ready.insert(rp.config).second) continue;
-        if ((st = resident_prepare(rp.config, rp.lds)) != FTWA_OK) return st;
-    }
-    if ((st = upload_shared(lat, shapes)) != FTWA_OK) return st;
-    return FTWA_OK;
+    const std::map<int, int> passes = shared_passes(lat->N, tab, &configs);
+    for (int c : configs)
+        if ((st = resident_prepare(c, 0)) != FTWA_OK) return st;
+    return upload_tables(lat, dev, shapes, passes);
 }
 
 ftwa_status ftwa_evolve_workspace_size(const ftwa_instance* inst, int n_inst, int64_t n_steps,

@@ -284,20 +284,20 @@ bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_tra
     return true;
 }
 
-std::vector<ResidentPlan> shared_plans(int N, const DeviceTables& tab) {
-    std::vector<ResidentPlan> all;
-    if (!tab.bipartite) return all;
-    ResidentPlan rp;
-    for (int var : {kSharedPlain, kSharedPot, kSharedHop, kSharedGint}) {
-        for (ftwa_dtype dtype : {FTWA_F64, FTWA_F32}) {
-            if (shared_many(N, dtype, tab, var, &rp)) all.push_back(rp);
-            for (int K : {1, 2, 4})
-                if (shared_few(N, dtype, tab, var, K, &rp)) all.push_back(rp);
-        }
-        for (int c = kSharedF64At; c < kSharedF32At + kSharedShapes; ++c)
-            if (shared_forced(c, N, tab, var, &rp)) all.push_back(rp);
-    }
-    return all;
+std::map<int, int> shared_passes(int N, const DeviceTables& tab, std::set<int>* configs) {
+    std::map<int, int> passes;
+    if (!tab.bipartite) return passes;
+    for (int c = kSharedF64At; c < kSharedF32At + kSharedShapes; ++c)
+        for (int var : {kSharedPlain, kSharedPot, kSharedHop, kSharedGint})
+            for (int K = 16; K >= 1; K /= 2) {
+                ResidentPlan rp;
+                if (!shared_fit(c, N, tab, var, K, &rp)) continue;
+                configs->insert(c);
+                const int n_pass = rp.workers / rp.lanes;
+                const auto it = passes.emplace(std::min(rp.lanes, 16), n_pass).first;
+                it->second = std::min(it->second, n_pass);
+            }
+    return passes;
 }
 
 bool resident_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, ResidentPlan* plan,

@@ -254,12 +254,12 @@ void rk4_shared(SharedArgs A) {
         const int N = E.N, NA = E.n_a;
         const int P = E.P;
         // the dealt lists (shared_lists): [2 N] sites by position and their
-        // neighbours' positions, then n_list even and n_list odd entries
+        // neighbours' positions, then `room` even and `room` odd entries
         // a | b << 8, all ones: none
         const uint32_t* const site = E.stab;
         const uint32_t* const nbp = E.stab + N;
         const uint32_t* const list = E.stab + 2 * N;
-        const int n_pass = NT >> ishift, n_list = U * n_pass;
+        const int n_pass = NT >> ishift, room = shared_room(ishift);
         const int S = shared_stride(N, NA, 1 << ishift);
         const int o_bb = NA * S, o_ab = N * S;
         // elements of a block, then M that stay zero (missing neighbours) and
@@ -296,7 +296,7 @@ void rk4_shared(SharedArgs A) {
 #pragma unroll
             for (int v = 0; v < 2 * U; ++v) {
                 const int x = (tid >> ishift) + n_pass * (v < U ? v : v - U);
-                const uint32_t w = list[(v < U ? 0 : n_list) + x];
+                const uint32_t w = list[(v < U ? 0 : room) + x];
                 const bool ok = w != 0xffffffffu;
                 const int a = ok ? (int)(w & 0xffu) : 0, b = ok ? (int)(w >> 8 & 0xffu) : 0;
                 const bool b_cls = v < U && a >= NA;  // BB
@@ -351,7 +351,7 @@ void rk4_shared(SharedArgs A) {
         // packed element of the state in HBM of slot v, spin index sp (false:
         // none); tr: its transpose
         auto state_at = [&](int v, int sp, int64_t& off, bool& tr) -> bool {
-            const uint32_t w = list[(v < U ? 0 : n_list) + (fresh(tid) >> ishift) +
+            const uint32_t w = list[(v < U ? 0 : room) + (fresh(tid) >> ishift) +
                                     n_pass * (v < U ? v : v - U)];
             const int64_t m = m0 + lq;
             if (w == 0xffffffffu || m >= Mc) return false;

@@ -6,6 +6,7 @@
 #include <array>
 #include <cstdint>
 #include <map>
+#include <set>
 #include <tuple>
 #include <mutex>
 #include <string>
@@ -49,6 +50,7 @@ struct DeviceTables {
                                // diagonal (the sites of one sublattice, ascending,
                                // then the other's)
     int n_a = 0;               // sites of the first sublattice
+    void* mem = nullptr;       // the allocation that holds every table of the lattice
     SplitShape split[kMaxParts + 1];  // by part count G = 2..kMaxParts (bipartite only)
     uint4* rdesc = nullptr;    // [2P][2]: descriptors of the on-chip reverse sweep with a
                                // packed X (N <= kReverseMaxSites; see reverse_descriptors)
@@ -91,25 +93,24 @@ struct ftwa_lattice_s {
     std::vector<uint8_t> sub;   // [N]
     std::mutex mu;
     std::map<int, ftwa::DeviceTables> dev;  // by HIP device ordinal
-    // resident-path descriptors padded per class to whole slots, by
-    // (device, even slots, odd slots, element bytes and diagonal layout)
-    std::map<std::tuple<int, int64_t, int64_t, int>, void*> padded;
-    // shared-pack lists by (device, lanes per element, entries per pass, entries)
-    // in one allocation per device
-    std::map<std::tuple<int, int, int, int>, const uint32_t*> shared;
-    std::map<int, void*> shared_dev;
+    // kernel tables by (device, parts, even slots, odd slots, boundary entry,
+    // element bytes and form), see TableShape
+    using TableKey = std::tuple<int, int, int64_t, int64_t, int64_t, int>;
+    struct Table {
+        const void* at = nullptr;
+        int part_words = 0, hmax = 0;
+    };
+    std::map<TableKey, Table> tables;
+    // shared-pack lists by (device, lanes per element, at most 16)
+    std::map<std::pair<int, int>, const uint32_t*> shared;
     std::vector<uint32_t> class_order;      // a | b << 16 of the stored elements in LDS-slot order
     std::vector<int32_t> diag_pos;          // site -> sublattice-major diagonal position
     std::vector<int32_t> rank;              // site -> bandwidth-reducing rank
-    // split-kernel tables by (device, parts, even slots, odd slots, boundary
-    // entry, element bytes): device blob, words per part, import capacity
-    std::map<std::tuple<int, int, int64_t, int64_t, int64_t, int>, std::tuple<void*, int, int>> split;
     // host part of the tables (class sizes, split shapes; no device pointers),
     // computed when the lattice is built
     ftwa::DeviceTables host;
-    // kernel tables ftwa_lattice_upload could not build, by split_key /
-    // padded_key: the error it met
-    std::map<std::string, std::pair<ftwa_status, std::string>> table_err;
+    // kernel tables ftwa_lattice_upload could not build: the error it met
+    std::map<TableKey, std::pair<ftwa_status, std::string>> table_err;
 };
 
 namespace ftwa {
@@ -152,22 +153,28 @@ const DeviceTables& host_tables(ftwa_lattice lat);
 // The lattice's device tables on the current device (FTWA_EINVAL unless
 // ftwa_lattice_upload ran there).
 ftwa_status device_tables(ftwa_lattice lat, DeviceTables* out);
-// Allocates and uploads the basic tables on the current device (idempotent).
-ftwa_status upload_tables(ftwa_lattice lat);
-std::string split_key(int dev, int G, int64_t even_slots, int64_t odd_slots, int64_t bnd_entry,
-                      int elem_bytes);
-std::string padded_key(int dev, int64_t even_slots, int64_t odd_slots, int elem_bytes,
-                       bool compact);
+// A table of a resident configuration: split_tables' for G > 1 parts, else
+// padded_descriptors'.
+struct TableShape {
+    int G = 1;
+    int64_t even_slots = 0, odd_slots = 0;
+    int64_t bnd_entry = 0;  // G > 1
+    int elem_bytes = 0;
+    bool compact = false;   // G = 1
+};
+// Builds every table of the lattice (the basic ones, those of `shapes`, and
+// the shared-pack lists for the lane counts of `passes`, each with the fewest
+// entries of a pass), in one allocation and one copy: 30 of each took 1.2 ms
+// of a 10-site lattice's 1.4.  Idempotent.
+ftwa_status upload_tables(ftwa_lattice lat, int dev, const std::vector<TableShape>& shapes,
+                          const std::map<int, int>& passes);
+bool uploaded(ftwa_lattice lat, int dev);
 // Descriptor table in LDS-slot order with the even class padded to
 // even_slots entries and the odd class to odd_slots entries; padding entries
 // own the scratch slot P+1 and read only the zero slot P.  compact selects
 // the 16-byte form of the spin-split kernels (else the wide form with
-// offsets for elem_bytes-byte elements).  Uploaded once per shape, element
-// size and form by ftwa_lattice_upload (create = true); the compute calls
-// only look it up.
-ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd_slots,
-                               int elem_bytes, bool compact, const void** out,
-                               bool create = false);
+// offsets for elem_bytes-byte elements).
+ftwa_status padded_descriptors(ftwa_lattice lat, const TableShape& shape, const void** out);
 
 // Row stride (in elements) of the shared-pack kernel's blocks where I lanes
 // share an element: at least the larger sublattice and odd (its own inverse
@@ -180,14 +187,18 @@ __host__ __device__ inline int shared_stride(int N, int n_a, int I) {
     while (I == 1 ? s % 16 != 7 && s % 16 != 9 : s % 2 == 0) ++s;
     return s;
 }
-// Lists of the shared-pack kernel where I lanes share an element: n_list
-// entries per class, the diagonal among the first n_pass (evolve_shared.h).
-ftwa_status shared_lists(ftwa_lattice lat, int I, int n_pass, int n_list, const uint32_t** out);
-// Uploads them for every {I, n_pass, n_list} of shapes (ftwa_lattice_upload).
-ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>>& shapes);
+// Lists of the shared-pack kernel where I lanes share an element: [2 N] sites
+// by position and their neighbours' positions, then shared_room even and as
+// many odd entries (evolve_shared.h), the same for every shape.
+ftwa_status shared_lists(ftwa_lattice lat, int I, const uint32_t** out);
+// Entries that the slots of the largest workgroup hold where 2^ishift lanes
+// share an element (ishift >= 4: one list for all).
+constexpr int kSharedSlots = 3072;
+__host__ __device__ inline int shared_room(int ishift) {
+    return kSharedSlots >> (ishift < 4 ? ishift : 4);
+}
 
-// Tables of the split resident kernel for G parts (uploaded once per shape by
-// ftwa_lattice_upload).
+// Tables of the split resident kernel for G parts.
 // One block of *part_words 32-bit words per part:
 //   [0..7]   n_even, n_own, n_import_even, n_import_odd, n_diag, 0, 0, 0
 //   [8..)    descriptors (compact form, 16 bytes per entry, even_slots +
@@ -203,9 +214,8 @@ ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>
 //            (halo slot n_own + h takes import h; even halo first)
 //   then     the site of even entry t < n_diag (its diagonal element)
 // then, after the G blocks, [N]: site -> part << 16 | slot of its diagonal element.
-ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t odd_slots,
-                         int64_t bnd_entry, int elem_bytes, const void** out, int* part_words,
-                         int* hmax, bool create = false);
+ftwa_status split_tables(ftwa_lattice lat, const TableShape& shape, const void** out,
+                         int* part_words, int* hmax);
 
 // ---------------------------------------------------------------- launches
 // Sampling of rho(0) for one instance (sample.hip).
@@ -411,8 +421,9 @@ int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int 
 bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_traj,
                  ResidentPlan* plan, int force_config, bool need_potential, bool need_hop,
                  bool need_interaction);
-// Every plan that shared_plan may return for a lattice (repetitions included).
-std::vector<ResidentPlan> shared_plans(int N, const DeviceTables& tab);
+// The shared-pack configurations that hold a lattice and, by lanes per element
+// (at most 16), the fewest entries of a pass among their plans.
+std::map<int, int> shared_passes(int N, const DeviceTables& tab, std::set<int>* configs);
 bool resident_is_shared(int config);
 size_t resident_mailbox_bytes(int config, int Nmax, int64_t n_items);
 ftwa_status resident_prepare(int config, size_t lds);  // host only, not under graph capture

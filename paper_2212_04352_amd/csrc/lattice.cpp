@@ -239,7 +239,7 @@ ftwa_status ftwa_lattice_info(ftwa_lattice lat, int* n_sites, int* n_bonds, cons
 
 void ftwa_free_lattice(ftwa_lattice lat) {
     if (!lat) return;
-    if (lat->dev.empty() && lat->padded.empty() && lat->split.empty() && lat->shared_dev.empty()) {
+    if (lat->dev.empty()) {
         delete lat;  // never uploaded: no HIP call
         return;
     }
@@ -247,25 +247,7 @@ void ftwa_free_lattice(ftwa_lattice lat) {
     (void)hipGetDevice(&cur);
     for (auto& [dev, tab] : lat->dev) {
         if (hipSetDevice(dev) != hipSuccess) continue;
-        (void)hipFree(tab.nb);
-        (void)hipFree(tab.off);
-        (void)hipFree(tab.elem);
-        if (tab.ord) (void)hipFree(tab.ord);
-        if (tab.dpos) (void)hipFree(tab.dpos);
-        if (tab.rdesc) (void)hipFree(tab.rdesc);
-        if (tab.rdescf) (void)hipFree(tab.rdescf);
-    }
-    for (auto& [key, ptr] : lat->padded) {
-        if (hipSetDevice(std::get<0>(key)) != hipSuccess) continue;
-        (void)hipFree(ptr);
-    }
-    for (auto& [key, val] : lat->split) {
-        if (hipSetDevice(std::get<0>(key)) != hipSuccess) continue;
-        (void)hipFree(std::get<0>(val));
-    }
-    for (auto& [dev, ptr] : lat->shared_dev) {
-        if (hipSetDevice(dev) != hipSuccess) continue;
-        (void)hipFree(ptr);
+        (void)hipFree(tab.mem);
     }
     if (cur >= 0) (void)hipSetDevice(cur);
     delete lat;
@@ -551,51 +533,61 @@ SplitShape split_shape(const std::vector<SplitPart>& parts) {
 
 }  // namespace
 
-std::string split_key(int dev, int G, int64_t even_slots, int64_t odd_slots, int64_t bnd_entry,
-                      int elem_bytes) {
-    return "s" + std::to_string(dev) + ":" + std::to_string(G) + ":" + std::to_string(even_slots) +
-           ":" + std::to_string(odd_slots) + ":" + std::to_string(bnd_entry) + ":" +
-           std::to_string(elem_bytes);
-}
+namespace {
 
-std::string padded_key(int dev, int64_t even_slots, int64_t odd_slots, int elem_bytes,
-                       bool compact) {
-    return "p" + std::to_string(dev) + ":" + std::to_string(even_slots) + ":" +
-           std::to_string(odd_slots) + ":" + std::to_string(elem_bytes) + ":" +
-           std::to_string(compact ? 1 : 0);
+// A lattice's table by device and shape.
+ftwa_lattice_s::TableKey table_key(int dev, const TableShape& sh) {
+    return {dev, sh.G, sh.even_slots, sh.odd_slots, sh.bnd_entry,
+            2 * sh.elem_bytes + (sh.compact ? 1 : 0)};
 }
 
 // A table that ftwa_lattice_upload could not build for this device: the
 // error it met then, else "not uploaded".
-ftwa_status missing_table(ftwa_lattice lat, const std::string& key) {
-    auto it = lat->table_err.find(key);
+ftwa_status missing_table(ftwa_lattice lat, int dev, const TableShape& sh) {
+    auto it = lat->table_err.find(table_key(dev, sh));
     if (it != lat->table_err.end()) return fail(it->second.first, it->second.second);
     return fail(FTWA_EINVAL,
                 "the lattice's kernel tables are not on this device: call ftwa_lattice_upload first");
 }
 
-ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t odd_slots,
-                         int64_t bnd_entry, int elem_bytes, const void** out, int* part_words,
-                         int* hmax, bool create) {
+}  // namespace
+
+ftwa_status split_tables(ftwa_lattice lat, const TableShape& sh, const void** out,
+                         int* part_words, int* hmax) {
+    int dev = 0;
+    FTWA_HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lock(lat->mu);
+    auto it = lat->tables.find(table_key(dev, sh));
+    if (it == lat->tables.end()) return missing_table(lat, dev, sh);
+    *out = it->second.at;
+    *part_words = it->second.part_words;
+    *hmax = it->second.hmax;
+    return FTWA_OK;
+}
+
+ftwa_status padded_descriptors(ftwa_lattice lat, const TableShape& sh, const void** out) {
+    int dev = 0;
+    FTWA_HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lock(lat->mu);
+    auto it = lat->tables.find(table_key(dev, sh));
+    if (it == lat->tables.end()) return missing_table(lat, dev, sh);
+    *out = it->second.at;
+    return FTWA_OK;
+}
+
+namespace {
+
+// The words of split_tables' table.
+ftwa_status split_words(ftwa_lattice lat, const TableShape& sh, std::vector<uint32_t>* out,
+                        int* part_words, int* hmax) {
+    const int G = sh.G, elem_bytes = sh.elem_bytes;
+    const int64_t even_slots = sh.even_slots, odd_slots = sh.odd_slots, bnd_entry = sh.bnd_entry;
     const DeviceTables& tab = host_tables(lat);
     if (!tab.bipartite) return fail(FTWA_ENOTSUP, "lattice is not bipartite");
     if (G < 2 || G > kMaxParts) return fail(FTWA_EINVAL, "split: part count out of range");
     const int N = lat->N;
     if (N > 256) return fail(FTWA_EINVAL, "split: more than 256 sites");
     if (even_slots % 64 || odd_slots % 64) return fail(FTWA_EINVAL, "split: slots not whole waves");
-    int dev = 0;
-    FTWA_HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(lat->mu);
-    const auto key = std::make_tuple(dev, G, even_slots, odd_slots, bnd_entry, elem_bytes);
-    auto it = lat->split.find(key);
-    if (it != lat->split.end()) {
-        *out = std::get<0>(it->second);
-        *part_words = std::get<1>(it->second);
-        *hmax = std::get<2>(it->second);
-        return FTWA_OK;
-    }
-    if (!create)
-        return missing_table(lat, split_key(dev, G, even_slots, odd_slots, bnd_entry, elem_bytes));
     const std::vector<uint32_t>& order = lat->class_order;
     const int64_t n = (int64_t)order.size();
     const std::vector<SplitPart> parts =
@@ -604,7 +596,8 @@ ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t od
     int H = 1;
     for (const SplitPart& sp : parts) H = std::max(H, (int)sp.halo.size());
     const int64_t pw = (8 + 4 * E + E + H + 256 + 3) / 4 * 4;
-    std::vector<uint32_t> blob((size_t)(pw * G + N), 0u);
+    std::vector<uint32_t>& blob = *out;
+    blob.assign((size_t)(pw * G + N), 0u);
     std::vector<int> part_q((size_t)n), slot_q((size_t)n);
     for (int p = 0; p < G; ++p) {
         const SplitPart& sp = parts[p];
@@ -661,13 +654,14 @@ ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t od
             bool exported;
             int a, b;
         };
-        std::vector<Ent> ent((size_t)E);
-        for (Ent& e : ent) {
-            for (int k = 0; k < 6; ++k) e.n[k] = Ref{-1, false};
-            e.own = Z0 + 32;  // padding entries own the scratch slot
-            e.exported = false;
-            e.a = e.b = -1;
-        }
+        // (most entries are padding: their passes keep `none`)
+        Ent none;
+        for (int k = 0; k < 6; ++k) none.n[k] = Ref{-1, false};
+        none.own = Z0 + 32;  // padding entries own the scratch slot
+        none.exported = false;
+        none.a = none.b = -1;
+        std::vector<Ent> ent((size_t)E, none);
+        std::vector<uint8_t> real((size_t)(E / R + 1), 0);  // passes that hold elements
         std::vector<uint8_t> is_export((size_t)n, 0);
         for (int pp = 0; pp < G; ++pp)
             if (pp != p)
@@ -676,6 +670,7 @@ ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t od
         auto fill = [&](int64_t q, int64_t at, bool gen) -> bool {
             const int a = (int)(order[q] & 0xffffu), b = (int)(order[q] >> 16);
             Ent& e = ent[(size_t)at];
+            real[(size_t)(at / R)] = 1;
             for (int k = 0; k < kMaxDeg; ++k) {
                 if (k < lat->deg[b]) e.n[k] = ref(a, lat->nbr[(size_t)b * kMaxDeg + k]);
                 if (k < lat->deg[a]) e.n[3 + k] = ref(lat->nbr[(size_t)a * kMaxDeg + k], b);
@@ -712,6 +707,7 @@ ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t od
         // (each class is a whole number of passes: even_slots is a multiple of 64)
         for (int64_t c0 = 0; c0 < E; c0 += R) {
             const int64_t c1 = std::min<int64_t>(c0 + R, E);
+            if (!real[(size_t)(c0 / R)]) continue;
             for (int k = 0; k < 6; ++k) {
                 uint32_t used = 0;
                 for (int64_t x = c0; x < c1; ++x)
@@ -729,6 +725,11 @@ ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t od
         uint32_t* dsite = imp + H;
         auto f = [](const Ref& r) { return (uint32_t)r.slot | (r.conj ? 0x8000u : 0u); };
         for (int64_t x = 0; x < E; ++x) {
+            if (!real[(size_t)(x / R)]) {  // padding: zero slots, the scratch slot
+                dsc[4 * x] = dsc[4 * x + 1] = dsc[4 * x + 2] = (uint32_t)Z0 * 0x10001u;
+                dsc[4 * x + 3] = (uint32_t)(Z0 + 32);
+                continue;
+            }
             const Ent& e = ent[(size_t)x];
             const uint32_t pi = e.a < 0 ? 0u : (uint32_t)lat->diag_pos[e.a];
             const uint32_t pj = e.b < 0 ? 0u : (uint32_t)lat->diag_pos[e.b];
@@ -746,18 +747,16 @@ ftwa_status split_tables(ftwa_lattice lat, int G, int64_t even_slots, int64_t od
     }
     uint32_t* dsrc = blob.data() + (size_t)G * pw;
     for (int i = 0; i < N; ++i) dsrc[i] = (uint32_t)part_q[(size_t)i] << 16 | (uint32_t)slot_q[(size_t)i];
-    void* d = nullptr;
-    FTWA_HIP_TRY(hipMalloc(&d, blob.size() * sizeof(uint32_t)));
-    FTWA_HIP_TRY(hipMemcpy(d, blob.data(), blob.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-    lat->split[key] = std::make_tuple(d, (int)pw, H);
-    *out = d;
     *part_words = (int)pw;
     *hmax = H;
     return FTWA_OK;
 }
 
-ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd_slots,
-                               int elem_bytes, bool compact, const void** out, bool create) {
+// The words of padded_descriptors' table.
+ftwa_status padded_words(ftwa_lattice lat, const TableShape& sh, std::vector<uint32_t>* out) {
+    const int64_t even_slots = sh.even_slots, odd_slots = sh.odd_slots;
+    const int elem_bytes = sh.elem_bytes;
+    const bool compact = sh.compact;
     const DeviceTables& tab = host_tables(lat);
     if (!tab.bipartite) return fail(FTWA_ENOTSUP, "lattice is not bipartite");
     const int N = lat->N;
@@ -769,17 +768,6 @@ ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd
         return fail(FTWA_EINVAL, "lattice too large for the resident layout");
     if (compact && (P + 33 > 0x8000 || N > 256))
         return fail(FTWA_EINVAL, "lattice too large for compact descriptors");
-    int dev = 0;
-    FTWA_HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(lat->mu);
-    const auto key =
-        std::make_tuple(dev, even_slots, odd_slots, elem_bytes * 2 + (compact ? 1 : 0));
-    auto it = lat->padded.find(key);
-    if (it != lat->padded.end()) {
-        *out = it->second;
-        return FTWA_OK;
-    }
-    if (!create) return missing_table(lat, padded_key(dev, even_slots, odd_slots, elem_bytes, compact));
     // LDS slot of every pair {i, j} (packed index of i <= j) and whether the
     // slot holds rho_ij (a = min) or rho_ji
     std::vector<uint32_t> slot((size_t)P);
@@ -820,17 +808,19 @@ ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd
         e.j = j;
         return e;
     };
-    std::vector<Sten> all((size_t)(even_slots + odd_slots));
-    {
-        Sten dummy;  // padding: reads the zero slot, owns the scratch slot
-        for (int n = 0; n < 6; ++n) dummy.n[n] = Ref{(uint32_t)P, false};
-        dummy.own = (uint32_t)(P + 1);
-        dummy.i = dummy.j = -1;
-        std::fill(all.begin(), all.end(), dummy);
-    }
+    // the entries up to the end of each class's last group of 32 (the rest is
+    // padding: it reads the zero slot and owns the scratch slot)
+    const int64_t room_even = std::min((n_even + 31) / 32 * 32, even_slots);
+    const int64_t room_odd = std::min((n_odd + 31) / 32 * 32, odd_slots);
+    const uint32_t scratch = (uint32_t)(compact ? P + 32 : P + 1);
+    Sten none;
+    for (int n = 0; n < 6; ++n) none.n[n] = Ref{(uint32_t)P, false};
+    none.own = scratch;
+    none.i = none.j = -1;
+    std::vector<Sten> all((size_t)(room_even + room_odd), none);
     for (int64_t q = 0; q < (int64_t)order.size(); ++q) {
         const int a = (int)(order[q] & 0xffffu), b = (int)(order[q] >> 16);
-        const int64_t at = q < n_even ? q : even_slots + (q - n_even);
+        const int64_t at = q < n_even ? q : room_even + (q - n_even);
         const Sten e = stencil(a, b);
         // past the leading groups no neighbour is a transpose (the kernel
         // reads those elements without the conjugation flags)
@@ -842,15 +832,24 @@ ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd
         if (e.own != (uint32_t)q) return fail(FTWA_ENOTSUP, "class order: element not stored");
         all[(size_t)at] = e;
     }
-    void* d = nullptr;
+    // the whole table, entries as `make` gives them
+    auto write = [&](auto kind, auto make) {
+        using V = decltype(kind);
+        out->resize((size_t)(even_slots + odd_slots) * (sizeof(V) / sizeof(uint32_t)));
+        V* const t = reinterpret_cast<V*>(out->data());
+        const V pad = make(none);
+        std::fill(t, t + even_slots + odd_slots, pad);
+        for (int64_t k = 0; k < room_even; ++k) t[k] = make(all[(size_t)k]);
+        for (int64_t k = 0; k < room_odd; ++k) t[even_slots + k] = make(all[(size_t)(room_even + k)]);
+    };
     if (compact) {
         // 32 zero slots P..P+31 (scratch P+32): the lanes of one 32-lane
         // group that read a missing neighbour read the zero slot whose LDS
         // bank no other lane of the group reads for that field, so the zero
         // reads cost no bank conflict
-        for (int64_t c0 = 0; c0 < even_slots + odd_slots; c0 += 32) {
-            const int64_t c1 = std::min<int64_t>(c0 + 32, c0 < even_slots ? even_slots
-                                                                          : even_slots + odd_slots);
+        for (int64_t c0 = 0; c0 < room_even + room_odd; c0 += 32) {
+            const int64_t c1 = std::min<int64_t>(c0 + 32, c0 < room_even ? room_even
+                                                                         : room_even + room_odd);
             for (int n = 0; n < 6; ++n) {
                 uint32_t used = 0;
                 for (int64_t k = c0; k < c1; ++k)
@@ -861,39 +860,29 @@ ftwa_status padded_descriptors(ftwa_lattice lat, int64_t even_slots, int64_t odd
                 for (int64_t k = c0; k < c1; ++k)
                     if (all[(size_t)k].n[n].slot == (uint32_t)P) all[(size_t)k].n[n].slot = z;
             }
-            for (int64_t k = c0; k < c1; ++k)
-                if (all[(size_t)k].own == (uint32_t)(P + 1)) all[(size_t)k].own = (uint32_t)(P + 32);
         }
-        std::vector<uint4> tabp(all.size());
         auto f = [](const Ref& r) { return r.slot | (r.conj ? 0x8000u : 0u); };
-        for (size_t k = 0; k < all.size(); ++k) {
-            const Sten& e = all[k];
+        write(uint4{}, [&](const Sten& e) {
             const uint32_t pi = e.i < 0 ? 0u : (uint32_t)lat->diag_pos[e.i];
             const uint32_t pj = e.j < 0 ? 0u : (uint32_t)lat->diag_pos[e.j];
-            tabp[k].x = f(e.n[0]) | f(e.n[1]) << 16;
-            tabp[k].y = f(e.n[2]) | f(e.n[3]) << 16;
-            tabp[k].z = f(e.n[4]) | f(e.n[5]) << 16;
-            tabp[k].w = e.own | pi << 16 | pj << 24;
-        }
-        FTWA_HIP_TRY(hipMalloc(&d, tabp.size() * sizeof(uint4)));
-        FTWA_HIP_TRY(hipMemcpy(d, tabp.data(), tabp.size() * sizeof(uint4), hipMemcpyHostToDevice));
+            return make_uint4(f(e.n[0]) | f(e.n[1]) << 16, f(e.n[2]) | f(e.n[3]) << 16,
+                              f(e.n[4]) | f(e.n[5]) << 16, e.own | pi << 16 | pj << 24);
+        });
     } else {
         const uint32_t eb = (uint32_t)elem_bytes;
-        std::vector<ResDesc> tabp(all.size());
         auto f = [&](const Ref& r) { return r.slot * eb | (r.conj ? 0x80000000u : 0u); };
-        for (size_t k = 0; k < all.size(); ++k) {
-            const Sten& e = all[k];
-            tabp[k].a = make_uint4(f(e.n[0]), f(e.n[1]), f(e.n[2]), e.own * eb);
-            tabp[k].b = make_uint4(f(e.n[3]), f(e.n[4]), f(e.n[5]), 0u);
-            if (e.i >= 0) tabp[k].b.w = ((uint32_t)e.i * eb) | (((uint32_t)e.j * eb) << 16);
-        }
-        FTWA_HIP_TRY(hipMalloc(&d, tabp.size() * sizeof(ResDesc)));
-        FTWA_HIP_TRY(hipMemcpy(d, tabp.data(), tabp.size() * sizeof(ResDesc), hipMemcpyHostToDevice));
+        write(ResDesc{}, [&](const Sten& e) {
+            ResDesc d;
+            d.a = make_uint4(f(e.n[0]), f(e.n[1]), f(e.n[2]), e.own * eb);
+            d.b = make_uint4(f(e.n[3]), f(e.n[4]), f(e.n[5]), 0u);
+            if (e.i >= 0) d.b.w = ((uint32_t)e.i * eb) | (((uint32_t)e.j * eb) << 16);
+            return d;
+        });
     }
-    lat->padded[key] = d;
-    *out = d;
     return FTWA_OK;
 }
+
+}  // namespace
 
 void compute_host_tables(ftwa_lattice lat) {
     DeviceTables& tab = lat->host;
@@ -971,6 +960,7 @@ struct SharedEntry {
     uint32_t code;      // a | b << 8
     uint32_t unit[8];
     uint8_t shape[7];   // elements 1..7 against element 0, modulo 16 (see shared_deal)
+    uint64_t hot[2];    // access x: bit 16 (x % 4) + its element modulo M of word x / 4
 };
 
 std::vector<SharedEntry> shared_entries(const ftwa_lattice_s& L, bool odd, int I) {
@@ -983,7 +973,9 @@ std::vector<SharedEntry> shared_entries(const ftwa_lattice_s& L, bool odd, int I
     };
     const int bb = n_a * S, ab = N * S;
     const uint32_t zero = (uint32_t)(((N + n_a) * S + 15) / 16 * 16);
+    const uint32_t mask = (uint32_t)(I >= 16 ? 1 : 16 / I) - 1;
     std::vector<SharedEntry> out;
+    out.reserve((size_t)packed_count(N));
     auto add = [&](int a, int b) {
         SharedEntry e;
         e.code = (uint32_t)a | (uint32_t)b << 8;
@@ -1015,6 +1007,8 @@ std::vector<SharedEntry> shared_entries(const ftwa_lattice_s& L, bool odd, int I
             const uint32_t of = !odd && k >= 4 && !missing ? (uint32_t)S * e.unit[0] : e.unit[0];
             e.shape[k - 1] = (uint8_t)(missing ? 16 : ((e.unit[k] - of) & 15u));
         }
+        e.hot[0] = e.hot[1] = 0;
+        for (int k = 0; k < 8; ++k) e.hot[k / 4] |= 1ull << (16 * (k % 4) + (e.unit[k] & mask));
         out.push_back(e);
     };
     if (odd) {
@@ -1055,18 +1049,21 @@ std::vector<uint32_t> shared_deal(const std::vector<SharedEntry>& all, size_t n_
         places[I == 8 ? k == 1 || k == 2 : kSide[k * (size_t)I / 4]].push_back(k);
     std::vector<std::vector<size_t>> groups;
     std::vector<size_t> g;
-    uint32_t used[8][16];
+    uint32_t used[8][16];  // [access][element modulo M], where taken says so
+    uint64_t taken[2];
     auto open_group = [&]() {
         g.clear();
-        std::memset(used, 0xff, sizeof(used));
+        taken[0] = taken[1] = 0;
     };
     auto fits = [&](size_t k, int limit) {
+        const SharedEntry& e = all[k];
         int c = 0;
-        for (int x = 0; x < 8 && c <= limit; ++x) {
-            const uint32_t u = all[k].unit[x], was = used[x][u & mask];
-            c += was != 0xffffffffu && was != u;
-        }
-        return c <= limit;
+        for (int h = 0; h < 2; ++h)
+            for (uint64_t meet = e.hot[h] & taken[h]; meet; meet &= meet - 1) {
+                const int bit = __builtin_ctzll(meet), x = 4 * h + bit / 16;
+                if (used[x][bit % 16] != e.unit[x] && ++c > limit) return false;
+            }
+        return true;
     };
     // up to `most` entries of `from` into the open group, those with at most
     // `limit` clashing accesses, looking at the first `window`
@@ -1076,6 +1073,7 @@ std::vector<uint32_t> shared_deal(const std::vector<SharedEntry>& all, size_t n_
             const size_t k = from[p];
             if (fits(k, limit)) {
                 for (int x = 0; x < 8; ++x) used[x][all[k].unit[x] & mask] = all[k].unit[x];
+                for (int h = 0; h < 2; ++h) taken[h] |= all[k].hot[h];
                 g.push_back(k);
             } else {
                 from[kept++] = k;
@@ -1140,11 +1138,11 @@ std::vector<uint32_t> shared_deal(const std::vector<SharedEntry>& all, size_t n_
 
 }  // namespace
 
-ftwa_status shared_lists(ftwa_lattice lat, int I, int n_pass, int n_list, const uint32_t** out) {
+ftwa_status shared_lists(ftwa_lattice lat, int I, const uint32_t** out) {
     int dev = 0;
     FTWA_HIP_TRY(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lock(lat->mu);
-    auto it = lat->shared.find(std::make_tuple(dev, I, n_pass, n_list));
+    auto it = lat->shared.find(std::make_pair(dev, std::min(I, 16)));
     if (it == lat->shared.end())
         return fail(FTWA_EINVAL,
                     "the lattice's tables are not on this device: call ftwa_lattice_upload first");
@@ -1152,86 +1150,46 @@ ftwa_status shared_lists(ftwa_lattice lat, int I, int n_pass, int n_list, const 
     return FTWA_OK;
 }
 
-ftwa_status upload_shared(ftwa_lattice lat, const std::vector<std::array<int, 3>>& shapes) {
-    int dev = 0;
-    FTWA_HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(lat->mu);
-    if (shapes.empty() || lat->shared_dev.count(dev)) return FTWA_OK;
-    const int N = lat->N;
-    std::vector<uint32_t> head((size_t)2 * N);  // sites, neighbours' positions
-    for (int i = 0; i < N; ++i) {
-        uint32_t w = 0xffffffu;
-        for (int k = 0; k < lat->deg[i]; ++k) {
-            w &= ~(0xffu << (8 * k));
-            w |= (uint32_t)lat->diag_pos[lat->nbr[(size_t)i * kMaxDeg + k]] << (8 * k);
-        }
-        head[lat->diag_pos[i]] = (uint32_t)i;
-        head[N + lat->diag_pos[i]] = w;
-    }
-    // One deal per class and lane count: the diagonal at the density that the
-    // shortest first pass needs.  They take 0.2 to 0.9 ms each at 54 sites, so
-    // they run side by side; below 32 sites a thread costs more than the deal.
-    const std::launch how = N < 32 ? std::launch::deferred : std::launch::async;
-    std::map<int, size_t> per;
-    for (const auto& [I, n_pass, n_list] : shapes) {
-        const size_t groups = (size_t)n_pass / (I >= 16 ? 1 : (size_t)(16 / I));
-        per[I] = std::max(per[I], ((size_t)N + groups - 1) / groups);
-    }
-    std::map<int, std::vector<uint32_t>> dealt[2];
-    try {
-        std::map<int, std::future<std::vector<uint32_t>>> dealing[2];
-        for (const auto& [I, density] : per)
-            for (int odd = 0; odd < 2; ++odd) {
-                auto deal = [lat, N, odd, I = I, density = density] {
-                    return shared_deal(shared_entries(*lat, odd != 0, I), odd ? 0 : (size_t)N, I,
-                                       density);
-                };
-                try {
-                    dealing[odd][I] = std::async(how, deal);
-                } catch (const std::system_error&) {  // no thread to be had
-                    dealing[odd][I] = std::async(std::launch::deferred, deal);
-                }
-            }
-        for (int odd = 0; odd < 2; ++odd)
-            for (auto& [I, f] : dealing[odd]) dealt[odd][I] = f.get();
-    } catch (const std::bad_alloc&) {
-        return fail(FTWA_ENOMEM, "dealing the shared-pack lists");
-    }
-    std::map<std::array<int, 3>, size_t> at;
-    std::vector<uint32_t> t;
-    for (const auto& shape : shapes) {
-        if (!at.emplace(shape, t.size()).second) continue;
-        t.insert(t.end(), head.begin(), head.end());
-        for (int odd = 0; odd < 2; ++odd) {
-            const std::vector<uint32_t>& list = dealt[odd][shape[0]];
-            const size_t end = t.size() + (size_t)shape[2];
-            if (list.size() > (size_t)shape[2])
-                return fail(FTWA_EINVAL, "shared-pack lists exceed their shape");
-            t.insert(t.end(), list.begin(), list.end());
-            t.resize(end, 0xffffffffu);
-        }
-    }
-    void* mem = nullptr;
-    FTWA_HIP_TRY(hipMalloc(&mem, t.size() * sizeof(uint32_t)));
-    if (hipMemcpy(mem, t.data(), t.size() * sizeof(uint32_t), hipMemcpyHostToDevice) !=
-        hipSuccess) {
-        (void)hipFree(mem);
-        return fail(FTWA_EHIP, "copying the shared-pack lists");
-    }
-    lat->shared_dev[dev] = mem;
-    for (const auto& [shape, off] : at)
-        lat->shared[std::make_tuple(dev, shape[0], shape[1], shape[2])] =
-            static_cast<const uint32_t*>(mem) + off;
-    return FTWA_OK;
-}
+namespace {
 
-ftwa_status upload_tables(ftwa_lattice lat) {
-    int dev = 0;
-    FTWA_HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(lat->mu);
-    if (lat->dev.count(dev)) return FTWA_OK;
+// The device tables of a lattice as one block of host memory, and where each
+// of them starts in it.
+struct Image {
+    std::vector<char> bytes;
+    size_t add(const void* p, size_t n) {
+        const size_t at = (bytes.size() + 255) / 256 * 256;
+        bytes.resize(at + n);
+        std::memcpy(bytes.data() + at, p, n);
+        return at;
+    }
+    template <typename V> size_t add(const std::vector<V>& v) { return add(v.data(), v.size() * sizeof(V)); }
+};
+
+ftwa_status upload_image(ftwa_lattice lat, int dev, const std::vector<TableShape>& shapes,
+                         const std::map<int, int>& passes) {
     const int N = lat->N;
     const int64_t P = packed_count(N);
+    // The deals of the shared-pack lists, one per class and lane count (16
+    // lanes and more want no order).  They take up to 2 ms each at 96 sites,
+    // so they run beside the other tables and each other; below 32 sites a
+    // thread costs more than the deal.
+    const std::launch how = N < 32 ? std::launch::deferred : std::launch::async;
+    std::map<int, std::future<std::vector<uint32_t>>> dealing[2];
+    for (const auto& [I, n_pass] : passes)
+        for (int odd = 0; odd < 2; ++odd) {
+            const size_t groups = (size_t)n_pass / (I >= 16 ? 1 : (size_t)(16 / I));
+            const size_t per = ((size_t)N + groups - 1) / groups;  // the diagonal's density
+            auto deal = [lat, N, odd, I = I, per] {
+                return shared_deal(shared_entries(*lat, odd != 0, I), odd ? 0 : (size_t)N, I, per);
+            };
+            try {
+                dealing[odd][I] = std::async(how, deal);
+            } catch (const std::system_error&) {  // no thread to be had
+                dealing[odd][I] = std::async(std::launch::deferred, deal);
+            }
+        }
+    Image im;
+    DeviceTables tab = lat->host;
     std::vector<int32_t> nb((size_t)N * 4), off(N);
     std::vector<uint32_t> elem((size_t)P);
     for (int i = 0; i < N; ++i) {
@@ -1240,32 +1198,100 @@ ftwa_status upload_tables(ftwa_lattice lat) {
         off[i] = (int32_t)packed_row(N, i);
         for (int j = i; j < N; ++j) elem[(size_t)(packed_row(N, i) + (j - i))] = (uint32_t)i | ((uint32_t)j << 16);
     }
-    DeviceTables tab = lat->host;
+    const size_t at_nb = im.add(nb), at_off = im.add(off), at_elem = im.add(elem);
+    size_t at_ord = 0, at_dpos = 0, at_rd[2] = {0, 0};
+    bool has_rd[2] = {false, false};
     if (tab.bipartite) {
-        const std::vector<uint32_t>& order = lat->class_order;
-        const std::vector<int32_t>& dpos = lat->diag_pos;
-        FTWA_HIP_TRY(hipMalloc(&tab.ord, order.size() * sizeof(uint32_t)));
-        FTWA_HIP_TRY(hipMemcpy(tab.ord, order.data(), order.size() * sizeof(uint32_t),
-                               hipMemcpyHostToDevice));
-        FTWA_HIP_TRY(hipMalloc(&tab.dpos, dpos.size() * sizeof(int32_t)));
-        FTWA_HIP_TRY(hipMemcpy(tab.dpos, dpos.data(), dpos.size() * sizeof(int32_t),
-                               hipMemcpyHostToDevice));
+        at_ord = im.add(lat->class_order);
+        at_dpos = im.add(lat->diag_pos);
     }
     for (int full = 0; full < 2; ++full) {
         if (N > (full ? kReverseFullMaxSites : kReverseMaxSites)) continue;
-        const std::vector<uint4> rd = reverse_descriptors(*lat, full != 0);
-        uint4*& dst = full ? tab.rdescf : tab.rdesc;
-        FTWA_HIP_TRY(hipMalloc(&dst, rd.size() * sizeof(uint4)));
-        FTWA_HIP_TRY(hipMemcpy(dst, rd.data(), rd.size() * sizeof(uint4), hipMemcpyHostToDevice));
+        at_rd[full] = im.add(reverse_descriptors(*lat, full != 0));
+        has_rd[full] = true;
     }
-    FTWA_HIP_TRY(hipMalloc(&tab.nb, nb.size() * sizeof(int32_t)));
-    FTWA_HIP_TRY(hipMalloc(&tab.off, off.size() * sizeof(int32_t)));
-    FTWA_HIP_TRY(hipMalloc(&tab.elem, elem.size() * sizeof(uint32_t)));
-    FTWA_HIP_TRY(hipMemcpy(tab.nb, nb.data(), nb.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    FTWA_HIP_TRY(hipMemcpy(tab.off, off.data(), off.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    FTWA_HIP_TRY(hipMemcpy(tab.elem, elem.data(), elem.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    std::map<ftwa_lattice_s::TableKey, std::pair<size_t, ftwa_lattice_s::Table>> made;
+    std::map<ftwa_lattice_s::TableKey, std::pair<ftwa_status, std::string>> failed;
+    std::vector<uint32_t> words;
+    for (const TableShape& sh : shapes) {
+        const auto key = table_key(dev, sh);
+        if (made.count(key) || failed.count(key)) continue;
+        ftwa_lattice_s::Table t;
+        const ftwa_status st = sh.G > 1 ? split_words(lat, sh, &words, &t.part_words, &t.hmax)
+                                        : padded_words(lat, sh, &words);
+        // a configuration that cannot hold the lattice after all: a plan that
+        // picks it reports the same error
+        if (st != FTWA_OK) failed[key] = std::make_pair(st, std::string(ftwa_last_error()));
+        else made[key] = std::make_pair(im.add(words), t);
+    }
+    std::map<int, size_t> at_list;
+    if (!passes.empty()) {
+        std::vector<uint32_t> head((size_t)2 * N);  // sites, neighbours' positions
+        for (int i = 0; i < N; ++i) {
+            uint32_t w = 0xffffffu;
+            for (int k = 0; k < lat->deg[i]; ++k) {
+                w &= ~(0xffu << (8 * k));
+                w |= (uint32_t)lat->diag_pos[lat->nbr[(size_t)i * kMaxDeg + k]] << (8 * k);
+            }
+            head[lat->diag_pos[i]] = (uint32_t)i;
+            head[N + lat->diag_pos[i]] = w;
+        }
+        for (const auto& [I, n_pass] : passes) {
+            const size_t room = (size_t)shared_room(__builtin_ctz((unsigned)I));
+            words = head;
+            for (int odd = 0; odd < 2; ++odd) {
+                const std::vector<uint32_t> list = dealing[odd][I].get();
+                if (list.size() > room) return fail(FTWA_EINVAL, "shared-pack lists exceed their room");
+                words.insert(words.end(), list.begin(), list.end());
+                words.resize((size_t)2 * N + room * (size_t)(odd + 1), 0xffffffffu);
+            }
+            at_list[I] = im.add(words);
+        }
+    }
+    void* mem = nullptr;
+    FTWA_HIP_TRY(hipMalloc(&mem, im.bytes.size()));
+    if (hipMemcpy(mem, im.bytes.data(), im.bytes.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipFree(mem);
+        return fail(FTWA_EHIP, "copying the lattice's tables");
+    }
+    char* const base = static_cast<char*>(mem);
+    tab.mem = mem;
+    tab.nb = reinterpret_cast<int32_t*>(base + at_nb);
+    tab.off = reinterpret_cast<int32_t*>(base + at_off);
+    tab.elem = reinterpret_cast<uint32_t*>(base + at_elem);
+    if (tab.bipartite) {
+        tab.ord = reinterpret_cast<uint32_t*>(base + at_ord);
+        tab.dpos = reinterpret_cast<int32_t*>(base + at_dpos);
+    }
+    if (has_rd[0]) tab.rdesc = reinterpret_cast<uint4*>(base + at_rd[0]);
+    if (has_rd[1]) tab.rdescf = reinterpret_cast<uint4*>(base + at_rd[1]);
+    for (auto& [key, t] : made) {
+        t.second.at = base + t.first;
+        lat->tables[key] = t.second;
+    }
+    for (const auto& [key, e] : failed) lat->table_err[key] = e;
+    for (const auto& [I, at] : at_list)
+        lat->shared[std::make_pair(dev, I)] = reinterpret_cast<const uint32_t*>(base + at);
     lat->dev[dev] = tab;
     return FTWA_OK;
+}
+
+}  // namespace
+
+bool uploaded(ftwa_lattice lat, int dev) {
+    std::lock_guard<std::mutex> lock(lat->mu);
+    return lat->dev.count(dev) != 0;
+}
+
+ftwa_status upload_tables(ftwa_lattice lat, int dev, const std::vector<TableShape>& shapes,
+                          const std::map<int, int>& passes) {
+    std::lock_guard<std::mutex> lock(lat->mu);
+    if (lat->dev.count(dev)) return FTWA_OK;
+    try {
+        return upload_image(lat, dev, shapes, passes);
+    } catch (const std::bad_alloc&) {
+        return fail(FTWA_ENOMEM, "the lattice's tables");
+    }
 }
 
 }  // namespace ftwa
