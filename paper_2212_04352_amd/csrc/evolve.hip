@@ -130,7 +130,7 @@ struct LaunchDesc {                // one resident launch: a group in a pass
 
 struct GroupPlan {
     int config = -1;
-    int threads = 0, units = 1, workers = 0;
+    int threads = 0, units = 1, workers = 0, variant = 0;
     size_t lds = 0;
     int Nmax = 0;
     bool by_record = false;        // one member, a launch per record interval
@@ -293,6 +293,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
                 g.threads = ip.res.threads;
                 g.units = ip.res.units;
                 g.workers = ip.res.workers;
+                g.variant = ip.res.variant;
                 g.by_record = ip.by_record;
                 p.groups.push_back(g);
             }
@@ -356,7 +357,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             // whole rounds of the trajectories the group runs at once
             const int64_t align = std::max<int64_t>(
                 1, resident_concurrency(ip.res.config, p.groups[ip.group].lds, ip.res.threads,
-                                        ip.res.units));
+                                        ip.res.units, ip.res.variant));
             c = (M + n_pass_goal - 1) / n_pass_goal;
             c = (c + align - 1) / align * align;
         }
@@ -419,11 +420,11 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             entry += L.n_entries;
             g.max_items = std::max(g.max_items, L.n_items);
             L.grid = resident_grid(g.config, g.lds, std::max<int64_t>(L.n_items, 1), g.threads,
-                                   g.units);
+                                   g.units, g.variant);
             if (n_inst > 1 && waits_for_none(g.config))
                 L.share = (double)L.grid * g.units /
                           (double)std::max<int64_t>(
-                              1, resident_concurrency(g.config, g.lds, g.threads, g.units));
+                              1, resident_concurrency(g.config, g.lds, g.threads, g.units, g.variant));
             p.launches.push_back(L);
         }
     p.n_table = entry;
@@ -1212,7 +1213,7 @@ ftwa_status plan_probe(const ftwa_instance& in, ftwa_dtype dtype, int probe_step
         ResidentPlan rp;
         if (!resident_plan(N, dtype, tab, &rp, c)) continue;
         pr.cands.push_back(c);
-        want = std::max(want, 2 * resident_concurrency(c, rp.lds, rp.threads, rp.units));
+        want = std::max(want, 2 * resident_concurrency(c, rp.lds, rp.threads, rp.units, rp.variant));
     }
     pr.cands.push_back(-1);
     if (want == 0) want = kStreamChunk;

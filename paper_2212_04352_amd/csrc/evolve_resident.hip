@@ -87,7 +87,11 @@ namespace {
 struct DeviceFacts {
     int cus = 0;
     std::set<int> prepared;
-    std::map<std::tuple<int, int, size_t>, int> per_cu;  // configuration, threads, LDS
+    std::map<std::tuple<int, int, size_t>, int> per_cu;  // configuration and variant, threads, LDS
+    // the shared-pack plan of an ensemble that fills the chip, by what it
+    // depends on (N, sites of the first sublattice, even elements, precision,
+    // variant): two dozen candidates weighed take 6 us
+    std::map<std::tuple<int, int, int64_t, int, int>, ResidentPlan> many;
 };
 constexpr size_t kMaxFacts = 4096;  // distinct launch shapes kept per device
 std::mutex g_facts_mu;
@@ -163,6 +167,7 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
     if (lds > kMaxLds) return false;
     *plan = ResidentPlan();
     plan->config = config;
+    plan->variant = var;
     plan->threads = (int)(nt + nd);
     plan->workers = (int)nt;
     plan->units = K;
@@ -178,8 +183,10 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
 // of the twelve that hide the LDS latency (20 sites FP32: two slots, packs of
 // 8, 7 waves 4.8e8 trajectory-steps/s; one slot, packs of 4, 14 waves 5.9e8),
 // where a pack of one leaves bank conflicts, for a single slot (the loads of
-// an element's neighbours have no other element's arithmetic beside them) and
-// for packed addresses.  Against a sweep of every shape and pack at 16, 20,
+// an element's neighbours have no other element's arithmetic beside them), for
+// packed addresses, and for interaction waves whose lanes have no site (30
+// sites FP32: packs of one 683 us, of two 475, the tiles 527; 4000
+// trajectories, 20 steps).  Against a sweep of every shape and pack at 16, 20,
 // 24, 30, 36, 40, 54, 66, 72 and 96 sites the choice is the fastest or within
 // 8 % of it (FP32 at 16 sites: within 30 %; general interaction: within 25 %).
 //
@@ -190,27 +197,33 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
 // (66 sites FP64 4.3e6; 96 sites FP32 9.6e6, the tiles 9.8e6).
 double shared_score(const ResidentPlan& rp, int N, int var) {
     const SharedShape& sh = *shared_at(rp.config);
-    const int waves = rp.threads / 64;
-    const int groups = std::min<int>(4 * sh.per_simd / waves, (int)(kMaxLds / rp.lds));
+    const int waves = rp.threads / 64, nd = rp.threads - rp.workers;
+    const double groups = (double)resident_concurrency(rp.config, rp.lds, rp.threads, rp.units,
+                                                       rp.variant) /
+                          ((double)rp.units * device_cus());
     const double fill = (double)packed_count(N) * rp.lanes / (2.0 * sh.U * rp.workers);
     const double busy = 0.6 + 0.4 * std::min(1.0, groups * waves / 12.0);
     double shape = 1.0;
     if (sh.packed) shape = var == kSharedHop ? 0.5 : sh.U > 3 ? 0.88 : 0.93;
     else if (sh.U == 1) shape = 0.88;
+    if (nd > 0) shape *= 0.5 + 0.5 * std::min(1.0, (double)rp.units * N / nd);
     return fill * busy * shape * (rp.units == 1 ? 0.95 : 1.0);
 }
 
 bool shared_allowed(int shape, int var) { return !(var == kSharedHop && shape == 5); }
 
-// The plan for an ensemble that fills the chip.
-bool shared_many(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, ResidentPlan* plan) {
+bool shared_many_uncached(int N, ftwa_dtype dtype, const DeviceTables& tab, int var,
+                          ResidentPlan* plan) {
     const bool f64 = dtype == FTWA_F64;
     const int at = f64 ? kSharedF64At : kSharedF32At;
     // Below 16 sites a stage is short and few waves per barrier matter more
     // than full slots: 12 sites, three slots, packs of 4 in one or two waves
     // 8.1e8 (FP64) and 1.58e9 (FP32) trajectory-steps/s, two slots, packs of
     // 16 in eleven 7.9e8 and 1.3e9; up to 11 sites one or two slots, packs of
-    // 4 in two waves: 1.23e9 and 2.37e9 at 10.  The waves of a general
+    // 4 in two waves: 1.23e9 and 2.37e9 at 10.  From 13 sites three slots take
+    // half as many waves more and fill them less than two (20000 trajectories,
+    // 40 steps, 14 sites: FP64 2.08 ms on three, 1.37 on two, the tiles 1.50;
+    // FP32 1.07, 0.69 and 0.88).  The waves of a general
     // interaction want larger packs (10 sites FP64: packs of 16 7.6e8, of 4
     // 5.5e8; 12 sites: 5.9e8 and 5.0e8; FP32 at 12: packs of 8 on one slot
     // 1.09e9, of 4 on three 8.5e8).
@@ -224,6 +237,9 @@ bool shared_many(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, Resi
             shape = !gint ? 3 : f64 ? 4 : 1;
             if (gint) K = f64 ? 16 : 8;
         }
+        if (shape == 3 && (!shared_fit(at + 3, N, tab, var, K, plan) ||
+                           plan->workers / plan->lanes > 16))
+            shape = 2;
         if (shared_fit(at + shape, N, tab, var, K, plan)) return true;
     }
     double best = 0;
@@ -241,20 +257,54 @@ bool shared_many(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, Resi
     return best > 0;
 }
 
+// The plan for an ensemble that fills the chip (config -1: none).
+bool shared_many(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, ResidentPlan* plan) {
+    int dev = 0;
+    const auto key = std::make_tuple(N, tab.n_a, tab.n_even, (int)dtype, var);
+    const bool known = hipGetDevice(&dev) == hipSuccess;
+    if (known) {
+        std::lock_guard<std::mutex> lock(g_facts_mu);
+        const auto& many = g_facts[dev].many;
+        const auto it = many.find(key);
+        if (it != many.end()) {
+            *plan = it->second;
+            return plan->config >= 0;
+        }
+    }
+    ResidentPlan rp;
+    if (!shared_many_uncached(N, dtype, tab, var, &rp)) rp.config = -1;
+    if (known) {
+        std::lock_guard<std::mutex> lock(g_facts_mu);
+        auto& many = g_facts[dev].many;
+        if (many.size() >= kMaxFacts) many.clear();
+        many[key] = rp;
+    }
+    *plan = rp;
+    return rp.config >= 0;
+}
+
 // The plan for an ensemble of fewer trajectories than that plan keeps in
 // flight: the smallest slots per thread that hold the lattice, packs of at
 // most K, small enough to give every CU one (a stage's latency is what
 // counts: 64 trajectories of 10 sites 0.24 us per stage with one slot against
-// 0.4 with three, 0.75 on the tiles above).
-bool shared_few(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, int K,
+// 0.4 with three, 0.75 on the tiles above).  wide: complex hopping with several
+// packs to a CU, where two slots come before one (its registers let two waves
+// of the one-slot kernel share a SIMD, three of the other: 13 sites FP32, 4000
+// trajectories 293 us on two slots, 334 on one, the tiles 312).
+bool shared_few(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, int K, bool wide,
                 ResidentPlan* plan) {
     const int at = dtype == FTWA_F64 ? kSharedF64At : kSharedF32At;
-    for (int shape : {0, 1, 2, 4, 5}) {
+    for (int shape : {0, wide ? 2 : 1, wide ? 1 : 2, 4, 5}) {
         if (!shared_allowed(shape, var) || (shape == 0 && K != 1)) continue;
         for (int k = K; k >= 1; k /= 2)
             if (shared_fit(at + shape, N, tab, var, k, plan)) return true;
     }
     return false;
+}
+
+// Whether a plan keeps n_traj trajectories in flight at once.
+bool shared_holds(const ResidentPlan& rp, int64_t n_traj) {
+    return n_traj <= resident_concurrency(rp.config, rp.lds, rp.threads, rp.units, rp.variant);
 }
 
 // A forced shape: the largest pack up to 4 that leaves room for the variant.
@@ -275,11 +325,26 @@ bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_tra
     const int var = shared_variant(need_potential, need_hop, need_interaction);
     if (force_config >= 0) return shared_forced(force_config, N, tab, var, plan);
     if (!shared_many(N, dtype, tab, var, plan)) return false;
-    if (n_traj < resident_concurrency(plan->config, plan->lds, plan->threads, plan->units)) {
+    if (n_traj < resident_concurrency(plan->config, plan->lds, plan->threads, plan->units,
+                                      plan->variant)) {
+        const int64_t cus = device_cus();
         int K = 1;
-        while (K < 4 && n_traj >= (int64_t)2 * K * device_cus()) K *= 2;
+        while (K < 4 && n_traj >= 2 * K * cus) K *= 2;
         ResidentPlan rp;
-        if (shared_few(N, dtype, tab, var, K, &rp)) *plan = rp;
+        if (!shared_few(N, dtype, tab, var, K, need_hop && N >= 12 && n_traj >= 4 * cus, &rp))
+            return true;
+        *plan = rp;
+        // a general interaction that this plan takes in turns: in packs of four
+        // if these are in flight all at once (30 sites FP64, 700 trajectories:
+        // 198 us, 270 in turns, the tiles 232)
+        if (need_interaction && !shared_holds(rp, n_traj))
+            for (int shape : {1, 2, 4, 5})
+                if (shared_fit((dtype == FTWA_F64 ? kSharedF64At : kSharedF32At) + shape, N, tab,
+                               var, 4, &rp) &&
+                    shared_holds(rp, n_traj)) {
+                    *plan = rp;
+                    break;
+                }
     }
     return true;
 }
@@ -458,10 +523,30 @@ int64_t spin_split_slots(const Config& c) {
     return c.G > 1 ? split_max_groups(c.G) : resident_max_pairs();
 }
 
-int64_t resident_concurrency(int config, size_t lds, int threads, int units) {
+// Workgroups of a kernel that a CU holds at once; false where the runtime does
+// not say.  A workgroup of more than four waves starts only where every SIMD
+// has room for its share rounded up, which the runtime's count leaves out (a
+// kernel that does nothing but wait, by waves per workgroup at three a SIMD:
+// 5 and 6 waves one workgroup, the runtime says two; at four a SIMD: 5 waves
+// two, it says three).  A persistent grid of the runtime's count then ran its
+// last third after the others had ended: 15 sites FP32, general interaction,
+// 4000 trajectories 483 us, 259 with the grid that fits.
+bool workgroups_per_cu(const void* fn, int threads, size_t lds, int* per_cu) {
+    int n = 0, waves = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds) != hipSuccess || n < 1)
+        return false;
+    if (threads > 256) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&waves, fn, 64, 0) != hipSuccess)
+            return false;
+        n = std::max(1, std::min(n, waves / 4 / ((threads / 64 + 3) / 4)));
+    }
+    *per_cu = n;
+    return true;
+}
+
+int64_t resident_concurrency(int config, size_t lds, int threads, int units, int variant) {
     const SharedShape* sh = shared_at(config);
     if (!sh && config_at(config).S == 1) return spin_split_slots(config_at(config));
-    const void* fn = sh ? sh->fn[kSharedPlain] : config_at(config).fn;
     // the occupancy query honours the dynamic-LDS limit of the kernel
     if (resident_prepare(config, kMaxLds) != FTWA_OK) return (int64_t)device_cus() * units;
     const int64_t cus = device_cus();
@@ -469,24 +554,33 @@ int64_t resident_concurrency(int config, size_t lds, int threads, int units) {
     if (hipGetDevice(&dev) != hipSuccess) return cus * units;
     std::lock_guard<std::mutex> lock(g_facts_mu);
     auto& known = g_facts[dev].per_cu;
-    const auto key = std::make_tuple(config, threads, lds);
+    const auto key = std::make_tuple(4 * config + variant, threads, lds);
     auto it = known.find(key);
     if (it != known.end()) return it->second * cus * units;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess ||
-        per_cu < 1)
+    if (sh) {
+        int t1 = 1;
+        if (!workgroups_per_cu(sh->fn[variant], threads, lds, &per_cu) ||
+            !workgroups_per_cu(sh->fn_t1[variant], threads, lds, &t1))
+            return cus * units;
+        per_cu = std::min(per_cu, t1);
+    } else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, config_at(config).fn, threads,
+                                                            lds) != hipSuccess ||
+               per_cu < 1) {
         return cus * units;
+    }
     if (known.size() >= kMaxFacts) known.clear();
     known.emplace(key, per_cu);
     return (int64_t)per_cu * cus * units;
 }
 
-int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int units) {
+int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int units,
+                      int variant) {
     if (!shared_at(config) && config_at(config).S == 1) {
         const Config& c = config_at(config);
         const int64_t n = std::min((n_items + 7) / 8 * 8, spin_split_slots(c));
         return 2 * (int64_t)c.G * n;
     }
-    const int64_t cap = resident_concurrency(config, lds, threads, units) / units;
+    const int64_t cap = resident_concurrency(config, lds, threads, units, variant) / units;
     return std::max<int64_t>(1, std::min(n_items, cap));
 }
 
@@ -500,7 +594,7 @@ size_t mailbox_words(const Config& c, int Nmax, int64_t grid) {
 size_t resident_mailbox_bytes(int config, int Nmax, int64_t n_items) {
     if (shared_at(config) || config_at(config).S != 1) return 0;
     const Config& c = config_at(config);
-    return mailbox_words(c, Nmax, resident_grid(config, 0, n_items, 0, 1)) * sizeof(uint64_t);
+    return mailbox_words(c, Nmax, resident_grid(config, 0, n_items, 0, 1, 0)) * sizeof(uint64_t);
 }
 
 

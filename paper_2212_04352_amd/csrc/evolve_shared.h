@@ -213,11 +213,17 @@ void rk4_shared(SharedArgs A) {
     const int lq = SPT == 1 ? (tid >> 1) & (K - 1) : tid & (K - 1);  // this lane's trajectory
     const int ls = SPT == 1 ? tid & 1 : 0;                           // and spin
 
-    // Workgroups are dealt round-robin to the eight XCDs: consecutive items
-    // (neighbouring trajectories, which share cache lines of the state) go to
-    // one XCD.
-    int64_t first = blockIdx.x;
-    if (gridDim.x % 8 == 0) first = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    // Workgroups are dealt round-robin to the eight XCDs: each XCD takes a run
+    // of consecutive items (neighbouring trajectories, which share cache lines
+    // of the state), an eighth of all, so that a last round that is not full
+    // is spread over the chip too.
+    int64_t first = blockIdx.x, stride = gridDim.x, end = A.n_items;
+    if (gridDim.x % 8 == 0) {
+        const int64_t share = (A.n_items + 7) / 8, xcd = blockIdx.x % 8;
+        first = xcd * share + blockIdx.x / 8;
+        stride = gridDim.x / 8;
+        end = (xcd + 1) * share < A.n_items ? (xcd + 1) * share : A.n_items;
+    }
 
     C y[2 * U][SPT], acc[2 * U][SPT], Y[2 * U][SPT];  // even slots, then odd slots
     // addresses: kAddr fields per slot (six neighbours, the element and its
@@ -246,7 +252,7 @@ void rk4_shared(SharedArgs A) {
     uint32_t wo[HOP ? 2 * U : 1];  // complex hopping: the two ratio triples' offsets
     int cur = -1;
 
-    for (int64_t item = first; item < A.n_items; item += gridDim.x) {
+    for (int64_t item = first; item < end; item += stride) {
         int ent = 0;
         while (ent + 1 < A.n_entries && A.table[ent + 1].item0 <= item) ++ent;
         ent = __builtin_amdgcn_readfirstlane(ent);

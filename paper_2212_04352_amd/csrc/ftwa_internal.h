@@ -323,6 +323,7 @@ struct ResidentPlan {
     int64_t odd_slots = 0;
     int workers = 0;         // shared-pack configurations: threads that own elements
     int lanes = 1;           // shared-pack configurations: lanes that share an element
+    int variant = 0;         // shared-pack configurations: the Hamiltonian's (evolve_shared.h)
     int64_t bnd_entry = 0;   // split configurations: first boundary entry of the even class
     size_t lds = 0;
     bool u_lds = false;      // shared blocks with a general interaction: lds includes a copy
@@ -412,9 +413,10 @@ ftwa_status umat_table(const double* u_mat, int N, ftwa_dtype dtype, void* out,
 ftwa_status hop_table(const double* hop_w, const int32_t* nb, const int32_t* dpos, int N,
                       int64_t n_steps, ftwa_dtype dtype, void* out, hipStream_t stream);
 int64_t resident_max_pairs();
-// trajectories in flight at once; threads, units: ResidentPlan's
-int64_t resident_concurrency(int config, size_t lds, int threads, int units);
-int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int units);
+// trajectories in flight at once; threads, units, variant: ResidentPlan's
+int64_t resident_concurrency(int config, size_t lds, int threads, int units, int variant);
+int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int units,
+                      int variant);
 // The shared-pack kernel's configuration (evolve_shared.h) for a lattice and
 // Hamiltonian variant and an ensemble of n_traj trajectories, or only
 // force_config's; false if none fits.

@@ -148,3 +148,28 @@ def test_automatic_choice(ft, orc, dtype, spec, variant):
         assert torch.equal(b.rho, c.rho)
         assert torch.allclose(b.S1, c.S1, rtol=1e-12, atol=1e-12)
         assert torch.allclose(b.S2, c.S2, rtol=1e-12, atol=1e-12)
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("spec", [_chain(3), _chain(13), ("armchair", 2, 7), ("torus", 3, 5)],
+                         ids=["chain3", "chain13", "armchair2x7", "torus3x5"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_ensembles_that_end_in_a_partial_round(ft, orc, dtype, spec, variant):
+    """Sizes next to the rules' lines; ensembles of a few packs more than run
+    at once, so that the last round of every XCD is short or empty."""
+    import torch
+    lat, olat = _lattices(ft, orc, spec, 1.0)
+    sub = np.asarray(lat.sub, dtype=float)
+    n0 = np.array([1.0 - sub, sub])
+    attrs, _ = _variant(variant, lat, olat, 6)
+    for M in (700, 4003):
+        print(f"{dtype} {variant} {lat.N} sites {M} trajectories", flush=True)
+        a = ft.Problem.allocate(lat, 3.3, M, n0, dtype)
+        ft.sample(a, 9)
+        b = _problem(ft, lat, n0, dtype, M, attrs, a.rho)
+        c = _problem(ft, lat, n0, dtype, M, attrs, a.rho)
+        ft.evolve(b, DT, STEPS, EVERY)
+        ft.evolve(c, DT, STEPS, EVERY, path="stream")
+        assert torch.equal(b.rho, c.rho)
+        assert torch.allclose(b.S1, c.S1, rtol=1e-12, atol=1e-12)
+        assert torch.allclose(b.S2, c.S2, rtol=1e-12, atol=1e-12)
