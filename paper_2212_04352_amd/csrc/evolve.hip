@@ -178,9 +178,66 @@ bool waits_for_none(int config) {
     return resident_is_shared(config) || resident_spins(config) == 2;
 }
 
+// Lattices of different sizes in one launch of the shared-pack kernel, in the
+// shape of the largest, where that takes fewer rounds of its packs than the
+// launches of their own would take together, a smaller lattice's round
+// counted by its elements (a quarter off: small lattices take more than that):
+// 54, 66, 72, 80 and 96 sites, 16 trajectories each, 40 steps: FP32 1.73 ms
+// -> 0.66, FP64 2.41 -> 1.81.
+void join_packs(const ftwa_instance* inst, Plan* p) {
+    for (int var = 0; var < kSharedVariants; ++var) {
+        std::vector<int> packs;
+        int lead = -1;
+        // the launches of their own: items, and the largest lattice
+        std::map<std::tuple<int, int, int, int>, std::pair<int64_t, int>> own;
+        for (int k = 0; k < p->n_inst; ++k) {
+            const InstPlan& ip = p->inst[k];
+            if (ip.path != FTWA_PATH_RESIDENT || !resident_is_shared(ip.res.config) ||
+                ip.res.variant != var)
+                continue;
+            packs.push_back(k);
+            auto& o = own[std::make_tuple(ip.res.config, ip.res.threads, ip.res.units,
+                                          ip.res.workers)];
+            o.first += (inst[k].n_traj + ip.res.units - 1) / ip.res.units;
+            if (o.second == 0 || inst[k].lat->N > inst[o.second - 1].lat->N) o.second = k + 1;
+            if (lead < 0 || inst[k].lat->N > inst[lead].lat->N) lead = k;
+        }
+        if (own.size() < 2) continue;
+        std::vector<ResidentPlan> as(packs.size());
+        const ResidentPlan& like = p->inst[lead].res;
+        size_t lds = 0;
+        int64_t items = 0;
+        bool fit = true;
+        for (size_t n = 0; n < packs.size() && fit; ++n) {
+            const ftwa_instance& in = inst[packs[n]];
+            fit = shared_plan_like(like, in.lat->N, host_tables(in.lat), &as[n]);
+            lds = std::max(lds, as[n].lds);
+            items += (in.n_traj + like.units - 1) / like.units;
+        }
+        if (!fit) continue;
+        auto rounds = [&](int64_t n_items, const ResidentPlan& rp, size_t bytes) {
+            const int64_t at_once = std::max<int64_t>(
+                1, resident_concurrency(rp.config, bytes, rp.threads, rp.units, var) / rp.units);
+            return (double)((n_items + at_once - 1) / at_once);
+        };
+        double apart = 0;
+        for (const auto& [key, o] : own) {
+            const InstPlan& ip = p->inst[o.second - 1];
+            apart += rounds(o.first, ip.res, ip.res.lds) *
+                     (double)packed_count(inst[o.second - 1].lat->N) /
+                     (double)packed_count(inst[lead].lat->N);
+        }
+        if (rounds(items, like, lds) > 0.75 * apart) continue;
+        for (size_t n = 0; n < packs.size(); ++n) p->inst[packs[n]].res = as[n];
+    }
+}
+
+// compact: as little workspace as possible (ftwa_evolve_static).  join: lattices
+// of different sizes share a launch where that is faster (not where the run's
+// groups may run side by side); needs no more workspace than without.
 ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_t n_steps,
                         int record_every, ftwa_dtype dtype, const ftwa_tuning* tune, Plan* out,
-                        bool compact = false) {
+                        bool compact = false, bool join = false) {
     if (dtype != FTWA_F64 && dtype != FTWA_F32) return fail(FTWA_EINVAL, "unknown dtype");
     if (n_steps < 0) return fail(FTWA_EINVAL, "n_steps < 0");
     if (record_every < 1) return fail(FTWA_EINVAL, "record_every < 1");
@@ -204,10 +261,17 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
                                                            : kInjectDropPartners;
 
     // ---- path and configuration of every instance
-    // (8 config + 4 (general interaction) + 2 (complex hopping) + (external
-    // potential), threads, units, workers, 1 + the instance if it is launched
-    // per record interval)
-    std::map<std::tuple<int, int, int, int, int>, int> group_of_config;
+    // Trajectories of the instances that would share a launch of the
+    // shared-pack kernel (a scan of parameters on one lattice): whether an
+    // ensemble fills the chip is asked of them together.
+    std::map<std::tuple<int, int, int64_t, int>, int64_t> together;
+    auto alike = [&](const ftwa_instance& in) {
+        const DeviceTables& tab = host_tables(in.lat);
+        return std::make_tuple(in.lat->N, tab.n_a, class_shape(tab),
+                               (in.v_site ? 1 : 0) + (in.hop_w ? 2 : 0) + (in.u_mat ? 4 : 0));
+    };
+    for (int k = 0; k < n_inst; ++k)
+        if (!inst[k].inv) together[alike(inst[k])] += inst[k].n_traj;
     for (int k = 0; k < n_inst; ++k) {
         InstPlan ip;
         const DeviceTables& tab = host_tables(inst[k].lat);
@@ -266,7 +330,8 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         // all was decided above.
         if (can_res && force < 0 && !tuned_tile && inst[k].inv == nullptr) {
             ResidentPlan sp;
-            if (shared_plan(N, dtype, tab, inst[k].n_traj, &sp, shared_cfg, pot, hop, gint))
+            if (shared_plan(N, dtype, tab, together[alike(inst[k])], &sp, shared_cfg, pot, hop,
+                            gint))
                 ip.res = sp;
         }
         if (force >= 0 && !can_res)
@@ -278,32 +343,42 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         if (want == FTWA_PATH_RESIDENT && !can_res)
             return fail(FTWA_ENOTSUP, "no resident configuration fits this lattice and dtype");
         ip.path = (want == FTWA_PATH_STREAM || !can_res) ? FTWA_PATH_STREAM : FTWA_PATH_RESIDENT;
-        if (ip.path == FTWA_PATH_RESIDENT) {
-            // instances with a potential form groups of their own: their
-            // launches run the potential variant, whose LDS layout holds the
-            // profile and is sized for it
-            const auto key = std::make_tuple(
-                8 * ip.res.config + (gint ? 4 : 0) + (hop ? 2 : 0) + (pot ? 1 : 0),
-                ip.res.threads, ip.res.units, ip.res.workers, ip.by_record ? 1 + k : 0);
-            auto it = group_of_config.find(key);
-            if (it == group_of_config.end()) {
-                it = group_of_config.emplace(key, (int)p.groups.size()).first;
-                GroupPlan g;
-                g.config = ip.res.config;
-                g.threads = ip.res.threads;
-                g.units = ip.res.units;
-                g.workers = ip.res.workers;
-                g.variant = ip.res.variant;
-                g.by_record = ip.by_record;
-                p.groups.push_back(g);
-            }
-            ip.group = it->second;
-            GroupPlan& g = p.groups[ip.group];
-            g.members.push_back(k);
-            g.lds = std::max(g.lds, ip.res.lds);
-            g.Nmax = std::max(g.Nmax, N);
-        }
         p.inst.push_back(ip);
+    }
+    if (join && force < 0) join_packs(inst, &p);
+
+    // ---- groups: instances of one launch
+    // (8 config + 4 (general interaction) + 2 (complex hopping) + (external
+    // potential), threads, units, workers, 1 + the instance if it is launched
+    // per record interval)
+    std::map<std::tuple<int, int, int, int, int>, int> group_of_config;
+    for (int k = 0; k < n_inst; ++k) {
+        InstPlan& ip = p.inst[k];
+        if (ip.path != FTWA_PATH_RESIDENT) continue;
+        // instances with a potential form groups of their own: their
+        // launches run the potential variant, whose LDS layout holds the
+        // profile and is sized for it
+        const auto key = std::make_tuple(
+            8 * ip.res.config + (inst[k].u_mat ? 4 : 0) + (inst[k].hop_w ? 2 : 0) +
+                (inst[k].v_site ? 1 : 0),
+            ip.res.threads, ip.res.units, ip.res.workers, ip.by_record ? 1 + k : 0);
+        auto it = group_of_config.find(key);
+        if (it == group_of_config.end()) {
+            it = group_of_config.emplace(key, (int)p.groups.size()).first;
+            GroupPlan g;
+            g.config = ip.res.config;
+            g.threads = ip.res.threads;
+            g.units = ip.res.units;
+            g.workers = ip.res.workers;
+            g.variant = ip.res.variant;
+            g.by_record = ip.by_record;
+            p.groups.push_back(g);
+        }
+        ip.group = it->second;
+        GroupPlan& g = p.groups[ip.group];
+        g.members.push_back(k);
+        g.lds = std::max(g.lds, ip.res.lds);
+        g.Nmax = std::max(g.Nmax, inst[k].lat->N);
     }
 
     // ---- stream instances: chunks of trajectories, one after another
@@ -1033,7 +1108,8 @@ ftwa_status ftwa_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
     ftwa_status st = check_instances(inst, n_inst, true, "ftwa_evolve");
     if (st != FTWA_OK) return st;
     Plan plan;
-    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan)) != FTWA_OK)
+    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, false,
+                          true)) != FTWA_OK)
         return st;
     if (workspace_bytes < plan.total || (!workspace && plan.total > 0))
         return fail(FTWA_EINVAL, "workspace smaller than ftwa_evolve_workspace_size");
@@ -1067,13 +1143,14 @@ ftwa_status ftwa_evolve_static(const ftwa_instance* inst, int n_inst, double dt,
     if (tune && tune->kernel_ms)
         return fail(FTWA_EINVAL, "ftwa_evolve_static: kernel timing is not available");
     Plan plan;
-    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan)) != FTWA_OK)
+    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, false,
+                          true)) != FTWA_OK)
         return st;
     // the split kernel's mailboxes are larger than a few trajectories' stream
-    // chunks, and groups that may run side by side have scratch of their own
+    // chunks, and groups have scratch of their own
     if (plan.total > kStaticScratchBytes &&
-        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, true)) !=
-            FTWA_OK)
+        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, true,
+                          true)) != FTWA_OK)
         return st;
     if (plan.total > kStaticScratchBytes)
         return fail(FTWA_EINVAL, "ftwa_evolve_static: this run needs " + std::to_string(plan.total) +

@@ -186,9 +186,10 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
 // an element's neighbours have no other element's arithmetic beside them), for
 // packed addresses, and for interaction waves whose lanes have no site (30
 // sites FP32: packs of one 683 us, of two 475, the tiles 527; 4000
-// trajectories, 20 steps).  Against a sweep of every shape and pack at 16, 20,
-// 24, 30, 36, 40, 54, 66, 72 and 96 sites the choice is the fastest or within
-// 8 % of it (FP32 at 16 sites: within 30 %; general interaction: within 25 %).
+// trajectories, 20 steps).  Against a sweep of every shape and pack at 25
+// lattices of 16 to 96 sites, all variants, the choice is within 9 % of the
+// fastest in 19 of 20 and within 21 % in all (the worst: 48 sites FP64 with a
+// general interaction).
 //
 // Complex hopping spills in the packed shapes: three packed slots serve only
 // where no other shape holds the lattice (66 sites: FP64 7.0e6
@@ -202,10 +203,10 @@ double shared_score(const ResidentPlan& rp, int N, int var) {
                                                        rp.variant) /
                           ((double)rp.units * device_cus());
     const double fill = (double)packed_count(N) * rp.lanes / (2.0 * sh.U * rp.workers);
-    const double busy = 0.6 + 0.4 * std::min(1.0, groups * waves / 12.0);
+    const double busy = 0.5 + 0.5 * std::min(1.0, groups * waves / 12.0);
     double shape = 1.0;
-    if (sh.packed) shape = var == kSharedHop ? 0.5 : sh.U > 3 ? 0.88 : 0.93;
-    else if (sh.U == 1) shape = 0.88;
+    if (sh.packed) shape = var == kSharedHop ? 0.5 : sh.U > 3 ? 0.88 : 0.89;
+    else if (sh.U == 1) shape = 0.8;
     if (nd > 0) shape *= 0.5 + 0.5 * std::min(1.0, (double)rp.units * N / nd);
     return fill * busy * shape * (rp.units == 1 ? 0.95 : 1.0);
 }
@@ -346,6 +347,18 @@ bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_tra
                     break;
                 }
     }
+    return true;
+}
+
+bool shared_plan_like(const ResidentPlan& like, int N, const DeviceTables& tab,
+                      ResidentPlan* plan) {
+    if (!shared_fit(like.config, N, tab, like.variant, like.units, plan) ||
+        plan->workers > like.workers)
+        return false;
+    plan->workers = like.workers;
+    plan->threads = like.threads;
+    plan->even_slots = plan->odd_slots =
+        (int64_t)shared_at(like.config)->U * (like.workers / like.lanes);
     return true;
 }
 

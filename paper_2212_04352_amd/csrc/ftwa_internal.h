@@ -423,6 +423,11 @@ int64_t resident_grid(int config, size_t lds, int64_t n_items, int threads, int 
 bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_traj,
                  ResidentPlan* plan, int force_config, bool need_potential, bool need_hop,
                  bool need_interaction);
+// The plan of another lattice in the shape, packs and threads of `like`; false
+// if they do not hold it.
+bool shared_plan_like(const ResidentPlan& like, int N, const DeviceTables& tab,
+                      ResidentPlan* plan);
+constexpr int kSharedVariants = 4;  // of the Hamiltonian (evolve_shared.h)
 // The shared-pack configurations that hold a lattice and, by lanes per element
 // (at most 16), the fewest entries of a pass among their plans.
 std::map<int, int> shared_passes(int N, const DeviceTables& tab, std::set<int>* configs);
