@@ -12,6 +12,7 @@
 // the grouping, the configuration or the pass split, so a batched run gives
 // bitwise the same trajectories as one run per instance.
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <set>
@@ -637,27 +638,24 @@ ftwa_status launch_by_record(const Plan& p, const ftwa_instance& in, int k, cons
     return FTWA_OK;
 }
 
-// Side branches of a captured run: streams that leave the main one after its
-// spin-split and split groups and join it at the end of the pass.
-constexpr int kSideStreams = 3;
-struct Fork {
-    hipStream_t side[kSideStreams] = {};
-    hipEvent_t out = nullptr, in[kSideStreams] = {};
-    bool create() {
-        bool ok = hipEventCreateWithFlags(&out, hipEventDisableTiming) == hipSuccess;
-        for (int i = 0; i < kSideStreams; ++i)
-            ok = ok && hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking) == hipSuccess &&
-                 hipEventCreateWithFlags(&in[i], hipEventDisableTiming) == hipSuccess;
-        return ok;
-    }
-    ~Fork() {
-        if (out) (void)hipEventDestroy(out);
-        for (int i = 0; i < kSideStreams; ++i) {
-            if (in[i]) (void)hipEventDestroy(in[i]);
-            if (side[i]) (void)hipStreamDestroy(side[i]);
-        }
-    }
-};
+// Side branches of a captured run: the nodes that the capturing stream's next
+// launch follows, read and set (streams and events of their own for the
+// branches took a third of a graph's creation).
+constexpr int kBranches = 3;
+using Nodes = std::vector<hipGraphNode_t>;
+ftwa_status capture_tail(hipStream_t stream, Nodes* tail) {
+    hipStreamCaptureStatus status;
+    const hipGraphNode_t* at = nullptr;
+    size_t n = 0;
+    FTWA_HIP_TRY(hipStreamGetCaptureInfo_v2(stream, &status, nullptr, nullptr, &at, &n));
+    tail->assign(at, at + n);
+    return FTWA_OK;
+}
+ftwa_status capture_after(hipStream_t stream, Nodes tail) {
+    FTWA_HIP_TRY(hipStreamUpdateCaptureDependencies(stream, tail.data(), tail.size(),
+                                                    hipStreamSetCaptureDependencies));
+    return FTWA_OK;
+}
 
 // Whether instances of different groups write to the same memory (slices of an
 // ensemble whose moments meet in one S1 and S2, say): such groups keep their
@@ -690,20 +688,23 @@ bool groups_share_outputs(const Plan& p, const ftwa_instance* inst) {
 }
 
 // Queues every launch of the run on `stream` (and nothing else: no host
-// synchronisation), so that it can be captured into a graph.  fork (with a
-// capture only): the groups whose workgroups wait for no other run side by
+// synchronisation), so that it can be captured into a graph.  fork (while the
+// library captures `stream` only): the groups whose workgroups wait for no other run side by
 // side once the spin-split and split groups are through (those fill the chip
 // and need their workgroups resident together), if the chip holds all their
-// workgroups at once, or nearly; otherwise persistent workgroups of several
-// kernels share CUs for the whole run.  Groups that write to the same memory stay
+// workgroups at once, or nearly, or in fewer rounds than there are groups of
+// one round each; otherwise persistent workgroups of several kernels share CUs
+// for the whole run.  Groups that write to the same memory stay
 // in order.  Graphs of six lattices of 10 to 96 sites, 64
 // trajectories each, 100 steps: FP32 2.81 ms one after another, 1.57 so; FP64
 // 5.08 and 3.20.  40, 54 and 66 sites FP64, 96 trajectories each, which take
 // somewhat more than the chip, 2.01 and 1.43.  24, 54 and 96 sites FP64, 256
-// each, twice the chip: 3.8 and 5.6; FP32 with 4096 each: 6.0 and 9.2.
+// each, twice the chip: 3.8 and 5.6; FP32 with 4096 each: 6.0 and 9.2.  54
+// sites FP32, the four Hamiltonian variants, 128 trajectories each, half the
+// chip (a CU holds one workgroup), 40 steps: 1.11 and 0.64.
 constexpr double kForkShare = 1.25;
 ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStream_t stream,
-                    KernelTimer& timer, bool cooperative, Fork* fork = nullptr) {
+                    KernelTimer& timer, bool cooperative, bool fork = false) {
     ftwa_status st;
     uint32_t* status = reinterpret_cast<uint32_t*>(ws + p.off_status);
     Prologue pro;
@@ -884,33 +885,42 @@ ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStrea
         std::vector<size_t> apart;  // the groups that run side by side
         if (may_fork) {
             double share = 0;
+            bool one_round = true;
             for (size_t gi = 0; gi < p.groups.size(); ++gi) {
                 const LaunchDesc& Ld = p.launches[(size_t)j * p.groups.size() + gi];
                 if (!waits_for_none(p.groups[gi].config) || Ld.n_items == 0) continue;
                 apart.push_back(gi);
                 share += Ld.share;
+                one_round = one_round && Ld.grid >= Ld.n_items;
             }
-            if (share > kForkShare) apart.clear();
+            if (share > kForkShare && (!one_round || std::ceil(share) >= (double)apart.size()))
+                apart.clear();
         }
         for (size_t gi = 0; gi < p.groups.size(); ++gi)
             if (std::find(apart.begin(), apart.end(), gi) == apart.end() &&
                 (st = launch_group(j, gi, stream)) != FTWA_OK)
                 return st;
-        if (!apart.empty()) FTWA_HIP_TRY(hipEventRecord(fork->out, stream));
+        Nodes base, tail[kBranches];  // before the branches, and of each
+        if (!apart.empty() && (st = capture_tail(stream, &base)) != FTWA_OK) return st;
         for (size_t n = 0; n < apart.size(); ++n) {
-            hipStream_t q = fork->side[n % kSideStreams];
-            if (n < kSideStreams) FTWA_HIP_TRY(hipStreamWaitEvent(q, fork->out, 0));
-            if ((st = launch_group(j, apart[n], q)) != FTWA_OK ||
-                (st = reduce_group(j, apart[n], q)) != FTWA_OK)
+            Nodes& branch = tail[n % kBranches];
+            if ((st = capture_after(stream, n < kBranches ? base : branch)) != FTWA_OK ||
+                (st = launch_group(j, apart[n], stream)) != FTWA_OK ||
+                (st = reduce_group(j, apart[n], stream)) != FTWA_OK ||
+                (st = capture_tail(stream, &branch)) != FTWA_OK)
                 return st;
         }
+        if (!apart.empty() && (st = capture_after(stream, base)) != FTWA_OK) return st;
         for (size_t gi = 0; gi < p.groups.size(); ++gi)
             if (std::find(apart.begin(), apart.end(), gi) == apart.end() &&
                 (st = reduce_group(j, gi, stream)) != FTWA_OK)
                 return st;
-        for (size_t n = 0; n < apart.size() && n < kSideStreams; ++n) {
-            FTWA_HIP_TRY(hipEventRecord(fork->in[n], fork->side[n]));
-            FTWA_HIP_TRY(hipStreamWaitEvent(stream, fork->in[n], 0));
+        if (!apart.empty()) {
+            Nodes all;
+            if ((st = capture_tail(stream, &all)) != FTWA_OK) return st;
+            if (all == base) all.clear();  // every branch follows it
+            for (const Nodes& t : tail) all.insert(all.end(), t.begin(), t.end());
+            if ((st = capture_after(stream, all)) != FTWA_OK) return st;
         }
     }
     // ---- non-finite trajectories counted by the invariant monitors
@@ -1195,16 +1205,10 @@ ftwa_status ftwa_evolve_graph(const ftwa_instance* inst, int n_inst, double dt, 
         delete g;
         return fail(FTWA_EHIP, "hipStreamCreateWithFlags");
     }
-    Fork fork;
-    if (!fork.create()) {
-        (void)hipStreamDestroy(cs);
-        delete g;
-        return fail(FTWA_EHIP, "streams of a graph's branches");
-    }
     KernelTimer off(false);
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-        st = execute(g->plan, g->inst.data(), g->ws, cs, off, false, &fork);
+        st = execute(g->plan, g->inst.data(), g->ws, cs, off, false, true);
         hipError_t e2 = hipStreamEndCapture(cs, &g->graph);
         if (st == FTWA_OK && e2 != hipSuccess) st = hip_fail(e2, "hipStreamEndCapture");
     } else {
