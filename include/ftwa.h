@@ -423,11 +423,13 @@ void ftwa_graph_free(ftwa_graph graph);
 
 /*
  * ftwa_autotune -- times every resident kernel configuration that fits each
- * distinct lattice of the instances (and the stream path) on a copy of the
- * instance's first trajectories (rho is not modified), `probe_steps` steps
- * each, and records the fastest per (device, lattice size, class sizes of
- * the lattice's stored elements, dtype); later plans with the automatic
- * choice use it.  configs (host, NULL or [n_inst])
+ * distinct lattice of the instances, the automatic choice and the stream path
+ * on a copy of the instance's first trajectories (rho is not modified),
+ * `probe_steps` steps each, and records the fastest per (device, lattice size,
+ * class sizes of the lattice's stored elements, dtype); later plans with the
+ * automatic choice use it.  Where the automatic choice of a small lattice (packs
+ * of trajectories sized by the ensemble) is the fastest, nothing is recorded
+ * and later plans stay automatic.  configs (host, NULL or [n_inst])
  * receives the choice per instance (-1 = stream path).  Synchronises
  * `stream`; must not be called under graph capture.  workspace: at least
  * ftwa_autotune_workspace_size bytes.

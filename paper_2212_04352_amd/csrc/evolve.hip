@@ -233,12 +233,16 @@ void join_packs(const ftwa_instance* inst, Plan* p) {
     }
 }
 
-// compact: as little workspace as possible (ftwa_evolve_static).  join: lattices
-// of different sizes share a launch where that is faster (not where the run's
-// groups may run side by side); needs no more workspace than without.
+struct PlanMode {
+    bool compact = false;  // as little workspace as possible (ftwa_evolve_static)
+    bool join = false;     // lattices of different sizes share a launch where that is
+                           // faster (not where the run's groups may run side by
+                           // side); needs no more workspace than without
+    bool untuned = false;  // without the autotuner's choices
+};
 ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_t n_steps,
                         int record_every, ftwa_dtype dtype, const ftwa_tuning* tune, Plan* out,
-                        bool compact = false, bool join = false) {
+                        const PlanMode& mode = PlanMode()) {
     if (dtype != FTWA_F64 && dtype != FTWA_F32) return fail(FTWA_EINVAL, "unknown dtype");
     if (n_steps < 0) return fail(FTWA_EINVAL, "n_steps < 0");
     if (record_every < 1) return fail(FTWA_EINVAL, "record_every < 1");
@@ -278,17 +282,18 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         const DeviceTables& tab = host_tables(inst[k].lat);
         const int N = inst[k].lat->N;
         int cfg = force;
-        int shared_cfg = -1;      // a tuned shared-pack configuration
-        bool tuned_tile = false;  // another resident configuration was tuned
+        bool tuned_tile = false;  // a resident configuration was faster than the packs
         bool tuned_stream = false;
-        if (cfg < 0 && want == FTWA_PATH_AUTO) {
-            int c = -1;
-            if (tuned_config(N, class_shape(tab), dtype, &c)) {
-                if (c < 0) tuned_stream = true;
-                if (resident_is_shared(c)) shared_cfg = c;
-                else cfg = c;
-                tuned_tile = c >= 0 && !resident_is_shared(c);
-            }
+        Tuned tuned;
+        if (cfg < 0 && want == FTWA_PATH_AUTO && !mode.untuned &&
+            tuned_config(N, class_shape(tab), dtype, &tuned)) {
+            // (a run that takes no packs where the tuned one would: one that is
+            // fast with few trajectories may be slow with many, 72 sites FP64
+            // with a general interaction tuned at 64 and run with 4000: 46.8
+            // ms, untuned 22.9)
+            if (!tuned.packs || together[alike(inst[k])] <= 2 * tuned.n_traj) cfg = tuned.config;
+            tuned_stream = cfg < 0 && !tuned.packs;
+            tuned_tile = cfg >= 0 && !tuned.packs;
         }
         // an external potential: the stream kernels, or a resident configuration
         // with the potential variant
@@ -324,15 +329,14 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         // FP64, 500 trajectories, 50 steps, 6 records: 48.0 ms there, 11.3 ms
         // so; 20 steps with a record after each 21.1 and 13.8 ms, with 64
         // trajectories 3.9 and 3.9 ms).
-        if (!can_res && inst[k].inv && !compact && force < 0 && want == FTWA_PATH_AUTO)
+        if (!can_res && inst[k].inv && !mode.compact && force < 0 && want == FTWA_PATH_AUTO)
             can_res = ip.by_record = fits(true);
         // Small lattices whose shared-pack form fits (with the instance's
         // variant) run there; whether the resident path takes the instance at
         // all was decided above.
-        if (can_res && force < 0 && !tuned_tile && inst[k].inv == nullptr) {
+        if (can_res && (force < 0 ? !tuned_tile && !inst[k].inv : resident_is_shared(force))) {
             ResidentPlan sp;
-            if (shared_plan(N, dtype, tab, together[alike(inst[k])], &sp, shared_cfg, pot, hop,
-                            gint))
+            if (shared_plan(N, dtype, tab, together[alike(inst[k])], &sp, force, pot, hop, gint))
                 ip.res = sp;
         }
         if (force >= 0 && !can_res)
@@ -346,7 +350,7 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         ip.path = (want == FTWA_PATH_STREAM || !can_res) ? FTWA_PATH_STREAM : FTWA_PATH_RESIDENT;
         p.inst.push_back(ip);
     }
-    if (join && force < 0) join_packs(inst, &p);
+    if (mode.join && force < 0) join_packs(inst, &p);
 
     // ---- groups: instances of one launch
     // (8 config + 4 (general interaction) + 2 (complex hopping) + (external
@@ -469,9 +473,9 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
             need = std::max(need, moments_workspace_bytes(2 * inst[k].lat->N, p.inst[k].chunk, p.n_rec));
         g.off_mom = off;
         r_mom = std::max(r_mom, need);
-        if (!compact) off = align_up(off + need);
+        if (!mode.compact) off = align_up(off + need);
     }
-    if (compact) off = align_up(off + r_mom);
+    if (mode.compact) off = align_up(off + r_mom);
     // launches and their table entries
     int64_t entry = 0;
     for (int j = 0; j < p.n_pass; ++j)
@@ -982,7 +986,7 @@ ftwa_status static_scratch(char** out) {
 
 // ---------------------------------------------------------------- tuning table
 std::mutex g_tune_mu;
-std::map<std::tuple<int, int, int64_t, int>, int> g_tuned;
+std::map<std::tuple<int, int, int64_t, int>, Tuned> g_tuned;
 
 int current_device() {
     int d = 0;
@@ -1044,17 +1048,17 @@ ftwa_status evolve_stored(const ftwa_instance& in, double dt, int64_t n_steps, i
     return check_status(ws, stream);
 }
 
-bool tuned_config(int N, int64_t shape, ftwa_dtype dtype, int* config) {
+bool tuned_config(int N, int64_t shape, ftwa_dtype dtype, Tuned* tuned) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tuned.find(std::make_tuple(current_device(), N, shape, (int)dtype));
     if (it == g_tuned.end()) return false;
-    *config = it->second;
+    *tuned = it->second;
     return true;
 }
 
-void set_tuned_config(int N, int64_t shape, ftwa_dtype dtype, int config) {
+void set_tuned_config(int N, int64_t shape, ftwa_dtype dtype, const Tuned& tuned) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    g_tuned[std::make_tuple(current_device(), N, shape, (int)dtype)] = config;
+    g_tuned[std::make_tuple(current_device(), N, shape, (int)dtype)] = tuned;
 }
 
 }  // namespace ftwa
@@ -1118,8 +1122,10 @@ ftwa_status ftwa_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
     ftwa_status st = check_instances(inst, n_inst, true, "ftwa_evolve");
     if (st != FTWA_OK) return st;
     Plan plan;
-    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, false,
-                          true)) != FTWA_OK)
+    PlanMode mode;
+    mode.join = true;
+    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, mode)) !=
+        FTWA_OK)
         return st;
     if (workspace_bytes < plan.total || (!workspace && plan.total > 0))
         return fail(FTWA_EINVAL, "workspace smaller than ftwa_evolve_workspace_size");
@@ -1153,14 +1159,17 @@ ftwa_status ftwa_evolve_static(const ftwa_instance* inst, int n_inst, double dt,
     if (tune && tune->kernel_ms)
         return fail(FTWA_EINVAL, "ftwa_evolve_static: kernel timing is not available");
     Plan plan;
-    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, false,
-                          true)) != FTWA_OK)
+    PlanMode mode;
+    mode.join = true;
+    if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, mode)) !=
+        FTWA_OK)
         return st;
     // the split kernel's mailboxes are larger than a few trajectories' stream
     // chunks, and groups have scratch of their own
+    mode.compact = true;
     if (plan.total > kStaticScratchBytes &&
-        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, true,
-                          true)) != FTWA_OK)
+        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, mode)) !=
+            FTWA_OK)
         return st;
     if (plan.total > kStaticScratchBytes)
         return fail(FTWA_EINVAL, "ftwa_evolve_static: this run needs " + std::to_string(plan.total) +
@@ -1254,8 +1263,16 @@ namespace {
 
 constexpr int kProbeReps = 3;
 
+// The untuned automatic plan as a candidate: where it is a pack of the
+// shared-pack kernel, whose size follows the ensemble and the Hamiltonian.
+// Where it is the fastest, later plans choose their packs by the rules again;
+// the best of the others serves the runs that have none.
+constexpr int kAutomatic = -2;
+
 struct Probe {
-    std::vector<int> cands;  // resident configurations that fit, then -1 (stream path)
+    std::vector<int> cands;  // resident configurations that fit (no packs), the automatic
+                             // plan if it is a pack, then -1 (stream path)
+    int pack = -1;           // the automatic plan's configuration, if it is a pack
     int64_t Mp = 0;          // trajectories timed
     size_t off_rho = 0, off_s1 = 0, off_s2 = 0, off_ws = 0, total = 0;
 };
@@ -1263,10 +1280,19 @@ struct Probe {
 ftwa_tuning probe_tuning(int cand) {
     ftwa_tuning t;
     std::memset(&t, 0, sizeof(t));
-    t.path = cand < 0 ? FTWA_PATH_STREAM : FTWA_PATH_RESIDENT;
+    t.path = cand == kAutomatic ? FTWA_PATH_AUTO : cand < 0 ? FTWA_PATH_STREAM
+                                                            : FTWA_PATH_RESIDENT;
     t.traj_chunk = 0;
-    t.resident_config = cand;
+    t.resident_config = std::max(cand, -1);
     return t;
+}
+
+ftwa_status plan_candidate(const ftwa_instance& q, ftwa_dtype dtype, int probe_steps, int cand,
+                           Plan* out) {
+    const ftwa_tuning t = probe_tuning(cand);
+    PlanMode mode;
+    mode.untuned = true;
+    return plan_evolve(&q, 1, 0.01, probe_steps, probe_steps, dtype, &t, out, mode);
 }
 
 ftwa_instance probe_instance(const ftwa_instance& in, int64_t Mp, char* ws, const Probe& pr) {
@@ -1292,9 +1318,21 @@ ftwa_status plan_probe(const ftwa_instance& in, ftwa_dtype dtype, int probe_step
     int64_t want = 0;
     for (int c = 0; c < resident_config_count(); ++c) {
         ResidentPlan rp;
-        if (!resident_plan(N, dtype, tab, &rp, c)) continue;
+        if (resident_is_shared(c) || !resident_plan(N, dtype, tab, &rp, c)) continue;
         pr.cands.push_back(c);
         want = std::max(want, 2 * resident_concurrency(c, rp.lds, rp.threads, rp.units, rp.variant));
+    }
+    {
+        Plan p;
+        const ftwa_instance q = probe_instance(in, std::max<int64_t>(in.n_traj, 1), nullptr, pr);
+        if ((st = plan_candidate(q, dtype, probe_steps, kAutomatic, &p)) != FTWA_OK) return st;
+        const ResidentPlan& rp = p.inst[0].res;
+        if (p.inst[0].path == FTWA_PATH_RESIDENT && resident_is_shared(rp.config)) {
+            pr.cands.push_back(kAutomatic);
+            pr.pack = rp.config;
+            want = std::max(want, 2 * resident_concurrency(rp.config, rp.lds, rp.threads, rp.units,
+                                                           rp.variant));
+        }
     }
     pr.cands.push_back(-1);
     if (want == 0) want = kStreamChunk;
@@ -1308,10 +1346,8 @@ ftwa_status plan_probe(const ftwa_instance& in, ftwa_dtype dtype, int probe_step
     size_t ews = 0;
     const ftwa_instance q = probe_instance(in, pr.Mp, nullptr, pr);
     for (int c : pr.cands) {
-        const ftwa_tuning t = probe_tuning(c);
         Plan p;
-        if ((st = plan_evolve(&q, 1, 0.01, probe_steps, probe_steps, dtype, &t, &p)) != FTWA_OK)
-            return st;
+        if ((st = plan_candidate(q, dtype, probe_steps, c, &p)) != FTWA_OK) return st;
         ews = std::max(ews, p.total);
     }
     pr.total = align_up(off + ews);
@@ -1379,13 +1415,11 @@ ftwa_status ftwa_autotune(const ftwa_instance* inst, int n_inst, ftwa_dtype dtyp
         const ftwa_instance q = probe_instance(in, pr.Mp, ws, pr);
         const size_t cb = cplx_bytes(dtype);
         const size_t P2 = (size_t)2 * packed_count(N);
-        int best = -1;
-        double best_ms = -1.0;
+        Tuned best;
+        double best_ms = -1.0, pack_ms = -1.0;
         for (int c : pr.cands) {
-            const ftwa_tuning t = probe_tuning(c);
             Plan p;
-            if ((st = plan_evolve(&q, 1, 0.01, probe_steps, probe_steps, dtype, &t, &p)) != FTWA_OK)
-                return done(st);
+            if ((st = plan_candidate(q, dtype, probe_steps, c, &p)) != FTWA_OK) return done(st);
             char* ews = ws + pr.off_ws;
             if ((st = build_table(p, &q, ews)) != FTWA_OK) return done(st);
             // one warm-up run, then the fastest of kProbeReps timed runs
@@ -1403,14 +1437,18 @@ ftwa_status ftwa_autotune(const ftwa_instance* inst, int n_inst, ftwa_dtype dtyp
                 if (rep > 0 && (ms < 0 || t < ms)) ms = t;
             }
             if ((st = check_status(ews, stream)) != FTWA_OK) return done(st);
-            if (best_ms < 0 || ms < best_ms) {
+            if (c == kAutomatic) {
+                pack_ms = ms;
+            } else if (best_ms < 0 || ms < best_ms) {
                 best_ms = ms;
-                best = c;
+                best.config = c;
             }
         }
+        best.packs = pack_ms >= 0 && pack_ms <= best_ms;
+        best.n_traj = in.n_traj;
         set_tuned_config(N, class_shape(tab), dtype, best);
-        decided[key] = best;
-        if (configs) configs[k] = best;
+        decided[key] = best.packs ? pr.pack : best.config;
+        if (configs) configs[k] = decided[key];
     }
     return done(FTWA_OK);
 }

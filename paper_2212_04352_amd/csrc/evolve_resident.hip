@@ -308,7 +308,8 @@ bool shared_holds(const ResidentPlan& rp, int64_t n_traj) {
     return n_traj <= resident_concurrency(rp.config, rp.lds, rp.threads, rp.units, rp.variant);
 }
 
-// A forced shape: the largest pack up to 4 that leaves room for the variant.
+// A forced shape that the rules do not choose: the largest pack up to 4 that
+// leaves room for the variant.
 bool shared_forced(int config, int N, const DeviceTables& tab, int var, ResidentPlan* plan) {
     for (int K = 4; K >= 1; K /= 2)
         if (shared_fit(config, N, tab, var, K, plan)) return true;
@@ -324,7 +325,15 @@ bool shared_plan(int N, ftwa_dtype dtype, const DeviceTables& tab, int64_t n_tra
                  bool need_interaction) {
     if (!tab.bipartite) return false;
     const int var = shared_variant(need_potential, need_hop, need_interaction);
-    if (force_config >= 0) return shared_forced(force_config, N, tab, var, plan);
+    if (force_config >= 0) {
+        // the plan of the rules, if that is its shape
+        if (shared_at(force_config)->dtype == dtype &&
+            shared_plan(N, dtype, tab, n_traj, plan, -1, need_potential, need_hop,
+                        need_interaction) &&
+            plan->config == force_config)
+            return true;
+        return shared_forced(force_config, N, tab, var, plan);
+    }
     if (!shared_many(N, dtype, tab, var, plan)) return false;
     if (n_traj < resident_concurrency(plan->config, plan->lds, plan->threads, plan->units,
                                       plan->variant)) {

@@ -436,14 +436,19 @@ size_t resident_mailbox_bytes(int config, int Nmax, int64_t n_items);
 ftwa_status resident_prepare(int config, size_t lds);  // host only, not under graph capture
 ftwa_status resident_launch(const ResidentLaunch& L, hipStream_t stream);
 
-// Configurations chosen by ftwa_autotune, per (device, N, even-class size, dtype).
-bool tuned_config(int N, int64_t shape, ftwa_dtype dtype, int* config);
+// What ftwa_autotune chose, per (device, N, even-class size, dtype).
+struct Tuned {
+    int config = -1;     // the fastest configuration that is no pack (-1: the stream path)
+    bool packs = false;  // the automatic packs were faster still
+    int64_t n_traj = 0;  // of the ensemble that was tuned
+};
+bool tuned_config(int N, int64_t shape, ftwa_dtype dtype, Tuned* tuned);
 // Resident run of one instance that stores its state at every record
 // (evolve.hip; ws == NULL: workspace size query into *bytes).
 ftwa_status evolve_stored(const ftwa_instance& in, double dt, int64_t n_steps, int record_every,
                           ftwa_dtype dtype, void* dump, int64_t dump_stride, char* ws,
                           size_t* bytes, hipStream_t stream);
-void set_tuned_config(int N, int64_t shape, ftwa_dtype dtype, int config);
+void set_tuned_config(int N, int64_t shape, ftwa_dtype dtype, const Tuned& tuned);
 
 // Brackets launches of the dominant kernel with HIP events on one stream and
 // sums their durations (optional, see ftwa_tuning::kernel_ms).
