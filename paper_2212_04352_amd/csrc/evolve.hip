@@ -1013,18 +1013,23 @@ ftwa_status evolve_stored(const ftwa_instance& in, double dt, int64_t n_steps, i
     // Packs of small lattices first, as in ordinary runs (whole gradients, 1024
     // trajectories, 200 steps: 54 sites FP32 stored every 50 steps 20.6 ms, on
     // the tiles 21.8, every 5 steps 22.8 and 25.2; FP64 37.0 and 38.7, 39.7 and
-    // 42.0; 12 sites FP32 2.9 and 3.7, 3.2 and 4.5).  Then the shared-block
-    // tiles with several trajectories per workgroup (their stores of
-    // neighbouring trajectories share cache lines; the single-unit tiles that
-    // ordinary runs prefer took the 54-site checkpoint run from 0.24 to
-    // 0.38 s), then the usual first fit (spin split, split kernel).
+    // 42.0; 12 sites FP32 2.9 and 3.7, 3.2 and 4.5), but not in five slots per
+    // thread, whose stores of a state take longer than its integration gains
+    // (40 steps stored one by one and 1024 trajectories FP32: 96 sites, five
+    // slots, 56.7 ms, on the tiles 49.3; 90 sites, three, 38.2 and 43.6).  Then
+    // the shared-block tiles with several trajectories per workgroup (their
+    // stores of neighbouring trajectories share cache lines; the single-unit
+    // tiles that ordinary runs prefer took the 54-site checkpoint run from 0.24
+    // to 0.38 s), then the usual first fit (spin split, split kernel).
     static const int kStoredPreference[] = {0, 13, 1, 23, 24, 14, 2, 15, 3,
                                             4, 16, 5, 17, 6, 18, 7};
     const DeviceTables& tab = host_tables(in.lat);
     ResidentPlan rp;
-    const bool packs = !in.inv && shared_plan(in.lat->N, dtype, tab, in.n_traj, &rp, -1,
-                                              in.v_site != nullptr, in.hop_w != nullptr,
-                                              in.u_mat != nullptr);
+    const bool packs = !in.inv &&
+                       shared_plan(in.lat->N, dtype, tab, in.n_traj, &rp, -1,
+                                   in.v_site != nullptr, in.hop_w != nullptr,
+                                   in.u_mat != nullptr) &&
+                       rp.even_slots < 5 * (rp.workers / rp.lanes);
     for (int c : kStoredPreference) {
         if (packs) break;
         if (resident_plan(in.lat->N, dtype, tab, &rp, c, in.inv == nullptr)) {
