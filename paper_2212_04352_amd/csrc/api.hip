@@ -46,13 +46,15 @@ __global__ __launch_bounds__(256) void occupation_kernel(int64_t count, double i
 // run together).  Consecutive rows go to one XCD, whose L2 joins the partial
 // lines at their ends.  198 sites, 8192 trajectories, FP32 (7.7 GB): 2.3 ms
 // (3.4 TB/s; a large copy reaches 4.7), with one thread per output element
-// gathering from the trajectory-innermost state 12.5 ms.
-template <typename C>
+// gathering from the trajectory-innermost state 12.5 ms.  TM: trajectories of a
+// block, 512 B of them, or 8 where there are no more (with 64 most lanes would
+// read nothing: 198 sites, 8 trajectories, FP32, ten calls 114 us, 107 so, which
+// is what their launches take).
+template <typename C, int TM>
 __global__ __launch_bounds__(256) void unpack_kernel(int N, int64_t n_traj, int64_t n_rows,
                                                      int64_t rows_per_xcd,
                                                      const C* __restrict__ rho,
                                                      C* __restrict__ out) {
-    constexpr int TM = 512 / (int)sizeof(C);  // trajectories of a block
     constexpr int TJ = 64;                    // columns of a block
     constexpr int RJ = 256 / TM;              // columns read at a time
     __shared__ C tile[TJ][TM + 1];
@@ -91,13 +93,18 @@ __global__ __launch_bounds__(256) void unpack_kernel(int N, int64_t n_traj, int6
     }
 }
 
+template <typename C, int TM>
+void launch_unpack_blocks(int N, int64_t n_traj, const void* rho, void* out, hipStream_t stream) {
+    const int64_t n_rows = (n_traj + TM - 1) / TM * 2 * N;
+    const int64_t per_xcd = (n_rows + 7) / 8;
+    hipLaunchKernelGGL((unpack_kernel<C, TM>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream,
+                       N, n_traj, n_rows, per_xcd, static_cast<const C*>(rho), static_cast<C*>(out));
+}
+
 template <typename C>
 void launch_unpack(int N, int64_t n_traj, const void* rho, void* out, hipStream_t stream) {
-    const int64_t tm = 512 / (int64_t)sizeof(C);
-    const int64_t n_rows = (n_traj + tm - 1) / tm * 2 * N;
-    const int64_t per_xcd = (n_rows + 7) / 8;
-    hipLaunchKernelGGL(unpack_kernel<C>, dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, N,
-                       n_traj, n_rows, per_xcd, static_cast<const C*>(rho), static_cast<C*>(out));
+    if (n_traj <= 8) launch_unpack_blocks<C, 8>(N, n_traj, rho, out, stream);
+    else launch_unpack_blocks<C, 512 / (int)sizeof(C)>(N, n_traj, rho, out, stream);
 }
 
 }  // namespace

@@ -30,3 +30,10 @@ def test_unpack_matches_layout(N, M, dtype):
     ft.ftwa_unpack(N, M, dtype, rho, out)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), unpack(packed, N))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("N,M", [(2, 8), (24, 7), (65, 8), (65, 9), (198, 2)])
+def test_unpack_of_few_trajectories(N, M, dtype):
+    """Both sides of the line at 8 trajectories between the block sizes."""
+    test_unpack_matches_layout(N, M, dtype)
