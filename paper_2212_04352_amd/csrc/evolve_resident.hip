@@ -690,6 +690,14 @@ ftwa_status umat_table(const double* u_mat, int N, ftwa_dtype dtype, void* out,
     return FTWA_OK;
 }
 
+namespace {
+// The flags and XCDs at the end of every split group's words.
+__global__ __launch_bounds__(64) void clear_sync_kernel(uint64_t* words, int64_t per_group) {
+    uint64_t* const sync = words + (blockIdx.x + 1) * per_group - kSplitSyncWords;
+    for (int k = threadIdx.x; k < kSplitSyncWords; k += 64) sync[k] = 0;
+}
+}  // namespace
+
 ftwa_status resident_launch(const ResidentLaunch& L, hipStream_t stream) {
     if (L.n_items <= 0) return FTWA_OK;
     if (const SharedShape* sh = shared_at(L.config)) {
@@ -738,10 +746,22 @@ ftwa_status resident_launch(const ResidentLaunch& L, hipStream_t stream) {
                                   : L.hopping   ? "this configuration has no complex-hopping variant"
                                                 : "this configuration has no external-potential variant");
     if (c.S == 1) {
-        // every word starts at stage 0, which no wait accepts (a fill kernel,
-        // no memset node)
-        ftwa_status st = zero_words(static_cast<unsigned*>(L.mailbox),
-                                    (int64_t)mailbox_words(c, L.Nmax, L.grid) * 2, stream);
+        // (fill kernels, no memset node.)  Spin split: every word starts at stage
+        // 0, which no wait accepts.  Split kernel: the flags at stage 0, no XCD;
+        // the published words are read only behind flags raised in this launch,
+        // so they keep what they hold (clearing them too, 0.8 MB a group, took
+        // 15 of the 640 us of a record interval of one step at 150 sites with
+        // 500 trajectories)
+        ftwa_status st = FTWA_OK;
+        if (c.G > 1) {
+            const int64_t groups = L.grid / (2 * c.G);
+            hipLaunchKernelGGL(clear_sync_kernel, dim3((unsigned)groups), dim3(64), 0, stream,
+                               static_cast<uint64_t*>(L.mailbox), split_words(c));
+            FTWA_LAUNCH_CHECK("clear_sync_kernel");
+        } else {
+            st = zero_words(static_cast<unsigned*>(L.mailbox),
+                            (int64_t)mailbox_words(c, L.Nmax, L.grid) * 2, stream);
+        }
         if (st != FTWA_OK) return st;
         // both workgroups of a pair must be resident at the same time: the
         // grid never exceeds one workgroup per CU; a cooperative launch checks
