@@ -94,10 +94,19 @@ __device__ __forceinline__ cplx_t<T> rhs_element(cplx_t<T> col, cplx_t<T> row, c
     return f;
 }
 
-// Runge-Kutta coefficient sets in the working precision (formed in FP64 and
-// rounded once).
-template <typename T> struct RKCoef {
-    T half, full, sixth, two;
-};
+// Byte offset = 16-bit field (low or high half of w) x 2^SH: one instruction
+// (a sub-dword operand select).
+template <int SH> __device__ __forceinline__ uint32_t lo16_shl(uint32_t w) {
+    uint32_t r;
+    __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
+            "src1_sel:WORD_0" : "=v"(r) : "v"(w), "i"(SH));
+    return r;
+}
+template <int SH> __device__ __forceinline__ uint32_t hi16_shl(uint32_t w) {
+    uint32_t r;
+    __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
+            "src1_sel:WORD_1" : "=v"(r) : "v"(w), "i"(SH));
+    return r;
+}
 
 }  // namespace ftwa

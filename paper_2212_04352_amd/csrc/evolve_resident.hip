@@ -152,8 +152,8 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
     // slot 0), two groups of entries (the first lanes clear the zero elements)
     const int64_t need = std::max<int64_t>({(most + sh.U - 1) / sh.U, N, I < 16 ? 32 / I : 1});
     const int64_t nt = (need * I + 63) / 64 * 64;
+    if (!sh.fn[var]) return false;
     // a general interaction: waves of their own for the sums D_i
-    if (var == kSharedGint && sh.maxt == 64) return false;
     const int64_t nd = var == kSharedGint ? std::min<int64_t>((K * N + 63) / 64 * 64, 192) : 0;
     if (nt + nd > sh.maxt) return false;
     if (K * N > shared_diag_cap(sh.maxt)) return false;
@@ -493,8 +493,9 @@ ftwa_status raise_lds_limit(int config) {
     if (const SharedShape* sh = shared_at(config)) {
         for (int v = 0; v < 4; ++v)
             for (const void* f : {sh->fn[v], sh->fn_t1[v]})
-                FTWA_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)kMaxLds));
+                if (f)
+                    FTWA_HIP_TRY(hipFuncSetAttribute(
+                        f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds));
         return FTWA_OK;
     }
     FTWA_HIP_TRY(hipFuncSetAttribute(config_at(config).fn,

@@ -13,9 +13,9 @@
 // conjugate transpose).  LDS holds the stage input of a pack of K = 2^k
 // trajectories: AA and BB as full squares, AB as a rectangle, rows S elements
 // apart, the pack's trajectories of an element side by side in units of 16
-// bytes (an element of both spins in FP32, of one in FP64: the other spin's
-// unit follows it where a thread works on one spin, SPT = 1, or lies 256
-// bytes further, units in runs of 16, where it works on both).  Nothing is
+// bytes: an element of both spins in FP32, of one in FP64 (the other spin's
+// unit follows it).  A thread works on both spins of an FP32 element or on one
+// (SPT), always on one of an FP64 element.  Nothing is
 // ever read as its conjugate:
 //   AB_ab:  col = sum_{k in nb(b)} AA_ak,  row = sum_{k in nb(a)} BB_kb;
 //   AA_aa': col = sum_{k in nb(a')} AB_ak, conj(row) = R = sum_{k in nb(a)} AB_a'k;
@@ -91,21 +91,6 @@ constexpr int shared_diag_cap(int maxt) { return maxt == 64 ? 64 : 320; }
 
 namespace shared_detail {
 
-// Byte offset = 16-bit field (low or high half of w) x 2^SH: one instruction
-// (a sub-dword operand select).
-template <int SH> __device__ __forceinline__ uint32_t lo16_shl(uint32_t w) {
-    uint32_t r;
-    __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-            "src1_sel:WORD_0" : "=v"(r) : "v"(w), "i"(SH));
-    return r;
-}
-template <int SH> __device__ __forceinline__ uint32_t hi16_shl(uint32_t w) {
-    uint32_t r;
-    __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-            "src1_sel:WORD_1" : "=v"(r) : "v"(w), "i"(SH));
-    return r;
-}
-
 template <typename T> struct Vec;
 template <> struct Vec<float> { typedef float type __attribute__((ext_vector_type(2))); };
 template <> struct Vec<double> { typedef double type __attribute__((ext_vector_type(2))); };
@@ -177,8 +162,7 @@ struct SharedShape {
     ftwa_dtype dtype;
     int U, spt, maxt;
     bool packed;    // addresses two to a register
-    int per_simd;   // waves that its registers let share a SIMD
-    const void* fn[4];
+    const void* fn[4];  // NULL: the shape has none
     const void* fn_t1[4];
 };
 constexpr int kSharedShapes = 6;  // of each precision
@@ -203,7 +187,7 @@ void rk4_shared(SharedArgs A) {
     constexpr uint32_t CB = sizeof(C), TB = sizeof(T);
     constexpr uint32_t kDg = shared_diag_cap(MAXT) * 2 * TB;  // one diagonal copy
     constexpr uint32_t kHead = shared_head(TB, MAXT, VAR);
-    constexpr uint32_t kSpin = F64 ? 256u : 8u;  // the other spin of a unit
+    static_assert(!F64 || SPT == 1, "an FP64 element's spins go to two lanes");
     extern __shared__ __align__(16) unsigned char smem[];  // dynamic LDS, at address 0
     (void)smem;
     const int tid = threadIdx.x;
@@ -275,9 +259,8 @@ void rk4_shared(SharedArgs A) {
         // LDS address of element e of this lane's trajectory (and spin)
         auto at = [&](int e) -> uint32_t {
             uint32_t unit = ((uint32_t)e << A.kshift) + (uint32_t)lq;
-            if constexpr (F64 && SPT == 1) unit = 2 * unit + (uint32_t)ls;
-            const uint32_t o = F64 && SPT == 2 ? (unit >> 4 << 9) + ((unit & 15u) << 4) : unit << 4;
-            return kHead + o + (!F64 && SPT == 1 ? 8u * (uint32_t)ls : 0u);
+            if constexpr (F64) unit = 2 * unit + (uint32_t)ls;
+            return kHead + (unit << 4) + (!F64 && SPT == 1 ? 8u * (uint32_t)ls : 0u);
         };
         const uint32_t tail =
             kHead + ((((uint32_t)(e_scr + M) << A.kshift) + 15u) & ~15u) * (F64 ? 32u : 16u);
@@ -376,16 +359,15 @@ void rk4_shared(SharedArgs A) {
                 z[s].x = v[s].x;
                 z[s].y = cj ? -v[s].y : v[s].y;
             }
-            if constexpr (SPT == 2 && !F64) {
+            if constexpr (SPT == 2) {
                 typedef float F4 __attribute__((ext_vector_type(4)));
                 lds_put<F4>(o, F4{z[0].x, z[0].y, z[SPT - 1].x, z[SPT - 1].y});
             } else {
-#pragma unroll
-                for (int s = 0; s < SPT; ++s) lds_put<C>(o + s * kSpin, z[s]);
+                lds_put<C>(o, z[0]);
             }
         };
         auto get = [&](uint32_t o, C* v) {
-            if constexpr (SPT == 2 && !F64) {
+            if constexpr (SPT == 2) {
                 typedef float F4 __attribute__((ext_vector_type(4)));
                 const F4 f = lds_get<F4>(o);
                 v[0].x = f.x;
@@ -393,8 +375,7 @@ void rk4_shared(SharedArgs A) {
                 v[SPT - 1].x = f.z;
                 v[SPT - 1].y = f.w;
             } else {
-#pragma unroll
-                for (int s = 0; s < SPT; ++s) v[s] = lds_get<C>(o + s * kSpin);
+                v[0] = lds_get<C>(o);
             }
         };
         // the diagonal element of slot 0 into a diagonal copy (and h = d + 1/2)
@@ -781,13 +762,22 @@ void rk4_shared(SharedArgs A) {
     }
 }
 
+// One wave has no room for the interaction's waves.
+template <typename T, int U, int SPT, int MAXT, int MINW, bool PF, bool PK, bool T1>
+constexpr const void* shared_gint_fn() {
+    if constexpr (MAXT > 64)
+        return (const void*)&rk4_shared<T, U, SPT, MAXT, MINW, PF, PK, T1, kSharedGint>;
+    else
+        return nullptr;
+}
+
 #define FTWA_SHARED_KERNELS(T, U, SPT, MAXT, MINW, PF, PK, T1)                       \
     {(const void*)&rk4_shared<T, U, SPT, MAXT, MINW, PF, PK, T1, kSharedPlain>,      \
      (const void*)&rk4_shared<T, U, SPT, MAXT, MINW, PF, PK, T1, kSharedPot>,        \
      (const void*)&rk4_shared<T, U, SPT, MAXT, MINW, PF, PK, T1, kSharedHop>,        \
-     (const void*)&rk4_shared<T, U, SPT, MAXT, MINW, PF, PK, T1, kSharedGint>}
-#define FTWA_SHARED(T, DT, U, SPT, MAXT, MINW, PF, PK, WAVES)                        \
-    SharedShape{DT, U, SPT, MAXT, PK, WAVES, FTWA_SHARED_KERNELS(T, U, SPT, MAXT, MINW, PF, PK, false), \
+     shared_gint_fn<T, U, SPT, MAXT, MINW, PF, PK, T1>()}
+#define FTWA_SHARED(T, DT, U, SPT, MAXT, MINW, PF, PK)                               \
+    SharedShape{DT, U, SPT, MAXT, PK, FTWA_SHARED_KERNELS(T, U, SPT, MAXT, MINW, PF, PK, false), \
                 FTWA_SHARED_KERNELS(T, U, SPT, MAXT, MINW, PF, PK, true)}
 
 }  // namespace ftwa

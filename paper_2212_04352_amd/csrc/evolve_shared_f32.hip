@@ -4,12 +4,12 @@
 namespace ftwa {
 
 const SharedShape kSharedF32[kSharedShapes] = {
-    FTWA_SHARED(float, FTWA_F32, 1, 1, 64, 1, false, false, 4),
-    FTWA_SHARED(float, FTWA_F32, 1, 2, 512, 1, false, false, 4),
-    FTWA_SHARED(float, FTWA_F32, 2, 2, 768, 1, false, false, 3),
-    FTWA_SHARED(float, FTWA_F32, 3, 2, 512, 1, true, false, 2),
-    FTWA_SHARED(float, FTWA_F32, 3, 2, 768, 1, false, true, 3),
-    FTWA_SHARED(float, FTWA_F32, 5, 2, 512, 1, false, true, 2),
+    FTWA_SHARED(float, FTWA_F32, 1, 1, 64, 1, false, false),
+    FTWA_SHARED(float, FTWA_F32, 1, 2, 512, 1, false, false),
+    FTWA_SHARED(float, FTWA_F32, 2, 2, 768, 1, false, false),
+    FTWA_SHARED(float, FTWA_F32, 3, 2, 512, 1, true, false),
+    FTWA_SHARED(float, FTWA_F32, 3, 2, 768, 1, false, true),
+    FTWA_SHARED(float, FTWA_F32, 5, 2, 512, 1, false, true),
 };
 
 }  // namespace ftwa

@@ -57,19 +57,6 @@ constexpr int kSplitSleep = 1;
 // trajectories: 8.7 -> 7.2 ms.  Reading an element ahead spills (198 sites 17.7
 // ms, 150 sites 13.8 ms).
 
-// Sub-dword-select shifts with the shift as a template argument.
-template <int SH> __device__ __forceinline__ uint32_t lo16_shl(uint32_t w) {
-    uint32_t r;
-    __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-            "src1_sel:WORD_0" : "=v"(r) : "v"(w), "i"(SH));
-    return r;
-}
-template <int SH> __device__ __forceinline__ uint32_t hi16_shl(uint32_t w) {
-    uint32_t r;
-    __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
-            "src1_sel:WORD_1" : "=v"(r) : "v"(w), "i"(SH));
-    return r;
-}
 template <int SH> __device__ __forceinline__ uint32_t b2_shl(uint32_t w) {
     uint32_t r;
     __asm__("v_lshlrev_b32_sdwa %0, %2, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD "
