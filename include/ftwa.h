@@ -397,11 +397,13 @@ ftwa_status ftwa_evolve_static(const ftwa_instance* inst, int n_inst, double dt,
  * ftwa_evolve (same arguments; kernel timing is not available) and captures
  * every launch of the run, the writes of its launch table into `workspace`
  * included, into a graph on a stream of its own; nothing is computed yet and
- * `stream` is not used.  Instances whose
- * kernel configuration is the same are integrated by one persistent kernel
- * per pass over a table of (instance, trajectory window) entries, so a batch
- * of mixed lattice sizes and U values needs a handful of kernel nodes; the
- * results are bitwise those of one ftwa_evolve per instance.
+ * `stream` is not used.  Instances whose kernel configuration is the same
+ * (for the packs of small lattices also their size and threads) are integrated
+ * by one persistent kernel per pass over a table of (instance, trajectory
+ * window) entries, and groups of instances that leave the GPU idle run side by
+ * side, so a batch of mixed lattice sizes and U values needs a handful of
+ * kernel nodes and little more than its slowest group's time; the results are
+ * bitwise those of one ftwa_evolve per instance.
  * ftwa_graph_launch queues the whole run on `stream` (one graph launch): it
  * re-zeroes S1/S2/inv and integrates the current rho for n_steps steps.  The
  * instance buffers and the workspace must stay allocated, and no other work

@@ -236,8 +236,7 @@ void join_packs(const ftwa_instance* inst, Plan* p) {
 struct PlanMode {
     bool compact = false;  // as little workspace as possible (ftwa_evolve_static)
     bool join = false;     // lattices of different sizes share a launch where that is
-                           // faster (not where the run's groups may run side by
-                           // side); needs no more workspace than without
+                           // faster (not where the run's groups may run side by side)
     bool untuned = false;  // without the autotuner's choices
 };
 ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_t n_steps,
@@ -1132,6 +1131,12 @@ ftwa_status ftwa_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
     if ((st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, mode)) !=
         FTWA_OK)
         return st;
+    // a joined launch's passes may be of other sizes than the ones asked for
+    mode.join = false;
+    if (workspace_bytes < plan.total &&
+        (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, mode)) !=
+            FTWA_OK)
+        return st;
     if (workspace_bytes < plan.total || (!workspace && plan.total > 0))
         return fail(FTWA_EINVAL, "workspace smaller than ftwa_evolve_workspace_size");
     hipStream_t stream = (hipStream_t)stream_;
@@ -1172,6 +1177,7 @@ ftwa_status ftwa_evolve_static(const ftwa_instance* inst, int n_inst, double dt,
     // the split kernel's mailboxes are larger than a few trajectories' stream
     // chunks, and groups have scratch of their own
     mode.compact = true;
+    mode.join = false;
     if (plan.total > kStaticScratchBytes &&
         (st = plan_evolve(inst, n_inst, dt, n_steps, record_every, dtype, tune, &plan, mode)) !=
             FTWA_OK)
