@@ -25,7 +25,7 @@ struct ResidentArgs {
 constexpr unsigned kSpinLimit = 1u << 26;  // default: ~2 s of polling
 constexpr int kSplitPlanePad = 8;  // spare words at the end of a split part's published planes
 constexpr int kSplitSyncWords = 80;  // words of a split group for its flags and its members' XCDs
-constexpr unsigned kSplitSpinLimit = 1u << 22;  // default: ~2 s at the sleeps between looks
+constexpr unsigned kSplitSpinLimit = 6u << 20;  // default: ~2 s at the sleeps between looks
 
 // Places whose complex-hopping ratios (three FP32 complex numbers, 24 bytes)
 // a stage keeps in LDS: the most that fit beside a 198-site spin block (its
