@@ -96,7 +96,8 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SOURCES = {"rk4_resident": ("rk4_resident.h", "device_common.h", "ftwa_internal.h"),
+KERNEL_SOURCES = {"rk4_resident": ("rk4_resident.h", "resident_config.h", "resident_f32_spin.hip",
+                                  "device_common.h", "ftwa_internal.h"),
                   "rk4_stage_stream": ("evolve_stream.hip", "device_common.h", "ftwa_internal.h")}
 
 

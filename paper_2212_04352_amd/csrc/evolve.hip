@@ -325,9 +325,9 @@ ftwa_status plan_evolve(const ftwa_instance* inst, int n_inst, double dt, int64_
         // automatic path launches them once per record interval and sums the
         // stored state in between: a launch reads and writes the state once,
         // where the stream kernels do so several times a stage (150 sites
-        // FP64, 500 trajectories, 50 steps, 6 records: 48.0 ms there, 11.3 ms
-        // so; 20 steps with a record after each 21.1 and 13.8 ms, with 64
-        // trajectories 3.9 and 3.9 ms).
+        // FP64, 500 trajectories, 50 steps, 6 records: 47.9 ms there, 9.3 ms
+        // so; 20 steps with a record after each 20.8 and 12.3 ms, with 64
+        // trajectories 3.8 and 3.3 ms).
         if (!can_res && inst[k].inv && !mode.compact && force < 0 && want == FTWA_PATH_AUTO)
             can_res = ip.by_record = fits(true);
         // Small lattices whose shared-pack form fits (with the instance's
@@ -697,14 +697,14 @@ bool groups_share_outputs(const Plan& p, const ftwa_instance* inst) {
 // and need their workgroups resident together), if the chip holds all their
 // workgroups at once, or nearly, or in fewer rounds than there are groups of
 // one round each; otherwise persistent workgroups of several kernels share CUs
-// for the whole run.  Groups that write to the same memory stay
-// in order.  Graphs of six lattices of 10 to 96 sites, 64
-// trajectories each, 100 steps: FP32 2.81 ms one after another, 1.57 so; FP64
-// 5.08 and 3.20.  40, 54 and 66 sites FP64, 96 trajectories each, which take
-// somewhat more than the chip, 2.01 and 1.43.  24, 54 and 96 sites FP64, 256
-// each, twice the chip: 3.8 and 5.6; FP32 with 4096 each: 6.0 and 9.2.  54
-// sites FP32, the four Hamiltonian variants, 128 trajectories each, half the
-// chip (a CU holds one workgroup), 40 steps: 1.11 and 0.64.
+// for the whole run.  Groups that write to the same memory stay in order.
+// Graphs of six lattices of 10 to 96 sites, 64 trajectories each, 100 steps:
+// FP32 2.80 ms one after another, 1.55 so; FP64 5.09 and 3.21.  40, 54 and 66
+// sites FP64, 96 trajectories each, which take somewhat more than the chip, 1.93
+// and 1.37.  24, 54 and 96 sites FP64, 256 each, twice the chip: 3.8 and 5.4;
+// FP32 with 4096 each, 20 steps: 6.0 and 9.0.  54 sites FP32, the four
+// Hamiltonian variants, 128 trajectories each, half the chip (a CU holds one
+// workgroup), 40 steps: 1.11 and 0.64.
 constexpr double kForkShare = 1.25;
 ftwa_status execute(const Plan& p, const ftwa_instance* inst, char* ws, hipStream_t stream,
                     KernelTimer& timer, bool cooperative, bool fork = false) {

@@ -181,7 +181,7 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
 // How well a plan suits an ensemble that fills the chip: the share of its
 // slots that hold elements, less where the resident waves of a CU fall short
 // of the twelve that hide the LDS latency (20 sites FP32: two slots, packs of
-// 8, 7 waves 4.8e8 trajectory-steps/s; one slot, packs of 4, 14 waves 5.9e8),
+// 8, 7 waves 5.0e8 trajectory-steps/s; one slot, packs of 4, 14 waves 6.0e8),
 // where a pack of one leaves bank conflicts, for a single slot (the loads of
 // an element's neighbours have no other element's arithmetic beside them), for
 // packed addresses, and for interaction waves whose lanes have no site (30
@@ -192,10 +192,10 @@ bool shared_fit(int config, int N, const DeviceTables& tab, int var, int K, Resi
 // general interaction).
 //
 // Complex hopping spills in the packed shapes: three packed slots serve only
-// where no other shape holds the lattice (66 sites: FP64 7.0e6
-// trajectory-steps/s, FP32 2.45e7, the tiles above 5.1e6 and 1.1e7; 40 sites
-// FP64 1.8e7 against 3.7e7 with two plain slots), the last shape never
-// (66 sites FP64 4.3e6; 96 sites FP32 9.6e6, the tiles 9.8e6).
+// where no other shape holds the lattice (66 sites FP64 7.8e6
+// trajectory-steps/s, the tiles above 5.2e6; 40 sites FP64 2.0e7 against 4.1e7
+// with two plain slots), the last shape never (66 sites FP64 4.3e6; 96 sites
+// FP32 1.03e7, the tiles 1.02e7).
 double shared_score(const ResidentPlan& rp, int N, int var) {
     const SharedShape& sh = *shared_at(rp.config);
     const int waves = rp.threads / 64, nd = rp.threads - rp.workers;
@@ -219,15 +219,15 @@ bool shared_many_uncached(int N, ftwa_dtype dtype, const DeviceTables& tab, int 
     const int at = f64 ? kSharedF64At : kSharedF32At;
     // Below 16 sites a stage is short and few waves per barrier matter more
     // than full slots: 12 sites, three slots, packs of 4 in one or two waves
-    // 8.1e8 (FP64) and 1.58e9 (FP32) trajectory-steps/s, two slots, packs of
-    // 16 in eleven 7.9e8 and 1.3e9; up to 11 sites one or two slots, packs of
-    // 4 in two waves: 1.23e9 and 2.37e9 at 10.  From 13 sites three slots take
+    // 8.2e8 (FP64) and 1.59e9 (FP32) trajectory-steps/s, two slots, packs of
+    // 16 in eleven 8.0e8 and 1.1e9; up to 11 sites one or two slots, packs of
+    // 4 in two waves: 1.38e9 and 2.36e9 at 10.  From 13 sites three slots take
     // half as many waves more and fill them less than two (20000 trajectories,
     // 40 steps, 14 sites: FP64 2.08 ms on three, 1.37 on two, the tiles 1.50;
-    // FP32 1.07, 0.69 and 0.88).  The waves of a general
-    // interaction want larger packs (10 sites FP64: packs of 16 7.6e8, of 4
-    // 5.5e8; 12 sites: 5.9e8 and 5.0e8; FP32 at 12: packs of 8 on one slot
-    // 1.09e9, of 4 on three 8.5e8).
+    // FP32 1.07, 0.69 and 0.88).  The waves of a general interaction want larger
+    // packs (10 sites FP64: packs of 16 7.8e8, of 4 5.8e8; 12 sites: 6.0e8, of 4
+    // on three slots 4.6e8; FP32 at 12: packs of 8 on one slot 1.14e9, of 4 on
+    // three 8.8e8).
     if (N < 16) {
         const bool gint = var == kSharedGint;
         int shape, K = 4;
@@ -287,8 +287,8 @@ bool shared_many(int N, ftwa_dtype dtype, const DeviceTables& tab, int var, Resi
 // The plan for an ensemble of fewer trajectories than that plan keeps in
 // flight: the smallest slots per thread that hold the lattice, packs of at
 // most K, small enough to give every CU one (a stage's latency is what
-// counts: 64 trajectories of 10 sites 0.24 us per stage with one slot against
-// 0.4 with three, 0.75 on the tiles above).  wide: complex hopping with several
+// counts: 64 trajectories of 10 sites FP64 0.23 us per stage with one slot, 0.45
+// with two, 0.66 with three, 0.74 on the tiles above).  wide: complex hopping with several
 // packs to a CU, where two slots come before one (its registers let two waves
 // of the one-slot kernel share a SIMD, three of the other: 13 sites FP32, 4000
 // trajectories 293 us on two slots, 334 on one, the tiles 312).
